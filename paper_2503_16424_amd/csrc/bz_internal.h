@@ -164,6 +164,11 @@ inline int64_t num_tiles(const bz_opts &o) {
     return o.batch ? o.batch->n_tiles : tiles_x(o) * tiles_y(o);
 }
 
+// Pixels of the canvas, or of all canvases of a batch.
+inline int64_t num_pixels(const bz_opts &o) {
+    return o.batch ? o.batch->n_pixels : (int64_t)o.width * o.height;
+}
+
 // Canvas of an index inside a batch: the last c whose offset (read by off)
 // is <= i, over the n_canvas + 1 records (empty canvases are skipped).
 template <typename Off>

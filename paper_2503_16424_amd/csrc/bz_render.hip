@@ -106,6 +106,7 @@ struct TileArgs {
     const float *l2_target;
     float *l2_grad;
     float *l2_loss;
+    int64_t l2_min_pairs;     // from so many pairs the blocks add to l2_loss themselves
     float l2_scale;
 };
 
@@ -520,8 +521,9 @@ __device__ inline float wave_sum(float v) {
 
 // The forward with the L2 loss gradient.  Every lane sums its squared errors
 // over the block's tiles; the block's waves add their sums in LDS and the last
-// one out adds the block's total to the loss, one global atomic per block.
-// Every wave of the block reaches the end exactly once (waves outside the
+// one out adds the block's total to the loss, one global atomic per block (or,
+// with fewer than l2_min_pairs pairs, a pass of its own over image and target
+// sums the loss afterwards).  Every wave of the block reaches the end exactly once (waves outside the
 // canvas leave fwd_tile early, not the kernel).
 template <bool kState, bool kCount>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_fwd_l2(TileArgs a) {
@@ -534,7 +536,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     __syncthreads();
     float l2 = 0.f;
     for_tiles(a, [&](int tile) { fwd_tile<kState, kCount, true>(a, tile, l2); });
-    if (!a.l2_loss) return;
+    if (!a.l2_loss || a.status[0] < a.l2_min_pairs) return;
     l2 = wave_sum(l2);
     if ((threadIdx.x & 63) == 0) {
         __hip_atomic_fetch_add(&s_loss, l2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1273,9 +1275,14 @@ __global__ void k_loss_zero(float *loss) {
     if (threadIdx.x == 0) loss[0] = 0.f;
 }
 
+// kGrad: also writes the gradient.  status (may be null): nothing is done from
+// max_pairs pairs on, where the forward has added up the loss.
+template <bool kGrad>
 __global__ __launch_bounds__(256) void k_l2(const float *__restrict__ img,
                                             const float *__restrict__ tgt, int64_t n, float scale,
-                                            float *__restrict__ d, float *loss) {
+                                            float *__restrict__ d, float *loss,
+                                            const int64_t *status, int64_t max_pairs) {
+    if (status && status[0] >= max_pairs) return;
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     float acc = 0.f;
@@ -1287,13 +1294,14 @@ __global__ __launch_bounds__(256) void k_l2(const float *__restrict__ img,
         const float4 a = reinterpret_cast<const float4 *>(img)[i];
         const float4 b = reinterpret_cast<const float4 *>(tgt)[i];
         const float4 e = make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w);
-        reinterpret_cast<float4 *>(d)[i] = make_float4(scale * e.x, scale * e.y, scale * e.z,
-                                                       scale * e.w);
+        if (kGrad)
+            reinterpret_cast<float4 *>(d)[i] = make_float4(scale * e.x, scale * e.y, scale * e.z,
+                                                           scale * e.w);
         acc = fmaf(e.x, e.x, fmaf(e.y, e.y, fmaf(e.z, e.z, fmaf(e.w, e.w, acc))));
     }
     for (int64_t i = 4 * n4 + t0; i < n; i += stride) {
         const float e = img[i] - tgt[i];
-        d[i] = scale * e;
+        if (kGrad) d[i] = scale * e;
         acc = fmaf(e, e, acc);
     }
     if (loss) {
@@ -1375,6 +1383,25 @@ TileArgs tile_args(const float *rec, const bz_bins &b, const bz_opts &o) {
 
 }  // namespace
 
+// Workgroups of an elementwise pass that ends in one atomic each on a single
+// word: more than ~256 and those same-address atomics, not HBM, set the time (at
+// 2048x2048: 27 us with 256, 33 with 1024, 62 with 4096).
+static int64_t l2_blocks(int64_t n) {
+    const int64_t blocks = cdiv(n, 4 * 256);
+    return blocks > 256 ? 256 : blocks;
+}
+
+// Who sums the loss.  The forward's blocks add theirs with one atomic each, 13
+// ns one after another on the one word: 140 us at 10,752 tiles, hidden under a
+// forward that takes longer (2,048 closed curves at 2040x1344, 257 pairs per tile:
+// 265 us, 287 with the sum as a pass of its own) and all of a forward that does
+// not (2,048 strokes, 25 pairs per tile: 144 us, 57 with the pass).  Up to
+// kLossTiles tiles (27 us of atomics) it is always the blocks; above, the pass
+// where there are fewer than kLossPairs pairs per tile, which only the device
+// knows.
+constexpr int kLossTiles = 2048;
+constexpr int64_t kLossPairs = 128;
+
 hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, float *image,
                       const bz_pixstate *st, const L2Out *l2, hipStream_t s) {
     TileArgs a = tile_args(rec, b, o);
@@ -1386,6 +1413,7 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
         a.l2_grad = l2->d_image;
         a.l2_loss = l2->loss;
         a.l2_scale = l2->scale;
+        a.l2_min_pairs = a.n_tiles > kLossTiles ? kLossPairs * (int64_t)a.n_tiles : 0;
         if (l2->loss) hipLaunchKernelGGL(k_loss_zero, dim3(1), dim3(64), 0, s, l2->loss);
     }
     if (st) {
@@ -1402,6 +1430,11 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
             launch_tiles(k_fwd_l2<true, true>, a, b, o, 0, threads, lds, s);
         else
             launch_tiles(k_fwd_l2<true, false>, a, b, o, 0, threads, lds, s);
+        if (l2->loss && a.l2_min_pairs > 0) {
+            const int64_t n = 3 * num_pixels(o);
+            hipLaunchKernelGGL(k_l2<false>, dim3(l2_blocks(n)), dim3(256), 0, s, image, l2->target,
+                               n, 0.f, (float *)nullptr, l2->loss, b.status, a.l2_min_pairs);
+        }
     } else {
         if (!st)
             launch_tiles(k_fwd<false, false>, a, b, o, 0, threads, lds, s);
@@ -1473,13 +1506,8 @@ hipError_t launch_l2(const float *image, const float *target, int64_t n, float s
                      float *d_image, float *loss, hipStream_t s) {
     if (loss) hipLaunchKernelGGL(k_loss_zero, dim3(1), dim3(64), 0, s, loss);
     if (n > 0) {
-        // every workgroup adds its partial loss to one word: more than ~256 of
-        // them and those same-address atomics, not HBM, set the time (at
-        // 2048x2048: 27 us with 256, 33 with 1024, 62 with 4096)
-        int64_t blocks = cdiv(n, 4 * 256);
-        if (blocks > 256) blocks = 256;
-        hipLaunchKernelGGL(k_l2, dim3(blocks), dim3(256), 0, s, image, target, n, scale, d_image,
-                           loss);
+        hipLaunchKernelGGL(k_l2<true>, dim3(l2_blocks(n)), dim3(256), 0, s, image, target, n, scale,
+                           d_image, loss, (const int64_t *)nullptr, (int64_t)0);
     }
     return hipGetLastError();
 }
