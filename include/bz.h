@@ -341,6 +341,21 @@ bz_status bz_render_bwd(const bz_curves *c, const bz_gaussians *g, const bz_bins
                         const bz_opts *opts, const float *d_image, const bz_pixstate *state,
                         bz_grads *grads, hipStream_t stream);
 
+/* bz_render_bwd with a scratch array to accumulate stage 1 in: 9 floats per
+ * Gaussian (bz_bwd_scratch_size bytes, device, 4-byte aligned, not d_gauss), contents
+ * irrelevant before and unspecified after the call.  All gradients, d_gauss among
+ * them, come out as from bz_render_bwd (up to the order of the float atomics);
+ * it is faster because a Gaussian's nine sums then share one or two memory lines.
+ * Argument errors as bz_render_bwd, plus BZ_ERR_ARG for a missing scratch and
+ * BZ_ERR_CAPACITY for one that is too small. */
+bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
+                                const bz_opts *opts, const float *d_image,
+                                const bz_pixstate *state, bz_grads *grads, float *scratch,
+                                int64_t scratch_bytes, hipStream_t stream);
+
+/* Host: bytes of scratch bz_render_bwd_scratch needs for n_gauss Gaussians. */
+bz_status bz_bwd_scratch_size(int64_t n_gauss, int64_t *bytes);
+
 /* Stage 1 of bz_render_bwd alone: per-Gaussian gradients into d_gauss (9 planes
  * of g->n floats, overwritten), the derivative of the blending of Sec. 3.4.
  * For callers that want gradients with respect to the Gaussians themselves. */

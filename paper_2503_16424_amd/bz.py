@@ -77,7 +77,7 @@ EXPORTS = ("bz_layout_host", "bz_workspace_size", "bz_num_tiles", "bz_batch_layo
            "bz_render_fwd", "bz_render_fwd_l2", "bz_render_bwd", "bz_render_bwd_gauss", "bz_render_bwd_curves",
            "bz_curve_area", "bz_area_order_workspace", "bz_area_order", "bz_xing_loss",
            "bz_l2_grad", "bz_status_str", "bz_peak_run", "bz_peak_work",
-           "bz_sample_bin_static")
+           "bz_sample_bin_static", "bz_bwd_scratch_size", "bz_render_bwd_scratch")
 
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024   # BZ_STATIC_SCRATCH_BYTES of bz.h
 
@@ -129,6 +129,12 @@ def load_library(path: str = LIB_PATH):
                                         C.c_void_p, C.c_void_p]
     lib.bz_render_bwd_curves.restype = C.c_int
     lib.bz_render_bwd_curves.argtypes = [P(Curves), P(Opts), C.c_void_p, P(Grads), C.c_void_p]
+    lib.bz_bwd_scratch_size.restype = C.c_int
+    lib.bz_bwd_scratch_size.argtypes = [C.c_int64, P(C.c_int64)]
+    lib.bz_render_bwd_scratch.restype = C.c_int
+    lib.bz_render_bwd_scratch.argtypes = [P(Curves), P(Gaussians), P(Bins), P(Opts), C.c_void_p,
+                                          P(PixState), P(Grads), C.c_void_p, C.c_int64,
+                                          C.c_void_p]
     lib.bz_curve_area.restype = C.c_int
     lib.bz_curve_area.argtypes = [P(Curves), C.c_void_p, C.c_void_p]
     lib.bz_area_order_workspace.restype = C.c_int
@@ -337,6 +343,9 @@ class Rasterizer:
         self.d_color = torch.empty_like(self.color)
         self.d_opacity = torch.empty_like(self.opacity)
         self.d_gauss = torch.empty(max(9 * self.n_gauss, 1), dtype=f32, device=self.dev)
+        sb = C.c_int64(0)
+        _check("bz_bwd_scratch_size", self.lib.bz_bwd_scratch_size(self.n_gauss, C.byref(sb)))
+        self.bwd_scratch = torch.empty(int(sb.value), dtype=torch.uint8, device=self.dev)
         self.grads = Grads(_ptr(self.d_ctrl).value, _ptr(self.d_width).value,
                            _ptr(self.d_color).value, _ptr(self.d_opacity).value,
                            _ptr(self.d_gauss).value)
@@ -491,10 +500,10 @@ class Rasterizer:
 
     def backward(self, d_image=None):
         d = self.d_image if d_image is None else d_image
-        _check("bz_render_bwd", self.lib.bz_render_bwd(C.byref(self.curves), C.byref(self.gauss),
-                                                       C.byref(self.bins), C.byref(self.opts),
-                                                       _ptr(d), self._state_arg(),
-                                                       C.byref(self.grads), _stream()))
+        _check("bz_render_bwd_scratch", self.lib.bz_render_bwd_scratch(
+            C.byref(self.curves), C.byref(self.gauss), C.byref(self.bins), C.byref(self.opts),
+            _ptr(d), self._state_arg(), C.byref(self.grads), _ptr(self.bwd_scratch),
+            self.bwd_scratch.numel(), _stream()))
 
     def backward_gauss(self, d_image=None):
         """Stage 1 only: per-Gaussian gradients into ``d_gauss``."""

@@ -335,9 +335,9 @@ bz_status bz_render_fwd_l2(const bz_gaussians *g, const bz_bins *b, const bz_opt
     return launched(launch_fwd(g->rec, *b, *o, image, state, &l2, s));
 }
 
-bz_status bz_render_bwd_gauss(const bz_gaussians *g, const bz_bins *b, const bz_opts *o,
-                              const float *d_image, const bz_pixstate *state, float *d_gauss,
-                              hipStream_t s) {
+static bz_status check_bwd_gauss(const bz_gaussians *g, const bz_bins *b, const bz_opts *o,
+                                 const float *d_image, const bz_pixstate *state,
+                                 const float *d_gauss) {
     bz_status st = check_opts(o);
     if (st != BZ_OK) return st;
     if (!g || g->n < 0 || (g->n > 0 && (!g->rec || !d_gauss))) return BZ_ERR_ARG;
@@ -346,12 +346,11 @@ bz_status bz_render_bwd_gauss(const bz_gaussians *g, const bz_bins *b, const bz_
     if ((st = check_state(state, o, b)) != BZ_OK) return st;
     if ((st = check_persistent(b, o)) != BZ_OK) return st;
     if (!(o->alpha_max < 1.f)) return BZ_ERR_UNSUPPORTED;
-    (void)hipGetLastError();
-    return launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, d_gauss, s));
+    return BZ_OK;
 }
 
-bz_status bz_render_bwd_curves(const bz_curves *c, const bz_opts *o, const float *d_gauss,
-                               bz_grads *gr, hipStream_t s) {
+static bz_status check_bwd_curves(const bz_curves *c, const bz_opts *o, const float *d_gauss,
+                                  const bz_grads *gr) {
     bz_status st = check_opts(o);
     if (st != BZ_OK) return st;
     if ((st = check_curves(c)) != BZ_OK) return st;
@@ -360,8 +359,24 @@ bz_status bz_render_bwd_curves(const bz_curves *c, const bz_opts *o, const float
         (!d_gauss || !gr->d_ctrl || !gr->d_width || !gr->d_color || !gr->d_opacity))
         return BZ_ERR_ARG;
     if (c->n_curves > 0 && stage2_lds(c) > kMaxLdsBytes) return BZ_ERR_UNSUPPORTED;
+    return BZ_OK;
+}
+
+bz_status bz_render_bwd_gauss(const bz_gaussians *g, const bz_bins *b, const bz_opts *o,
+                              const float *d_image, const bz_pixstate *state, float *d_gauss,
+                              hipStream_t s) {
+    bz_status st = check_bwd_gauss(g, b, o, d_image, state, d_gauss);
+    if (st != BZ_OK) return st;
     (void)hipGetLastError();
-    return launched(launch_bwd_curves(*c, *o, d_gauss, *gr, s));
+    return launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, d_gauss, false, s));
+}
+
+bz_status bz_render_bwd_curves(const bz_curves *c, const bz_opts *o, const float *d_gauss,
+                               bz_grads *gr, hipStream_t s) {
+    bz_status st = check_bwd_curves(c, o, d_gauss, gr);
+    if (st != BZ_OK) return st;
+    (void)hipGetLastError();
+    return launched(launch_bwd_curves(*c, *o, d_gauss, nullptr, *gr, s));
 }
 
 bz_status bz_render_bwd(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
@@ -374,6 +389,33 @@ bz_status bz_render_bwd(const bz_curves *c, const bz_gaussians *g, const bz_bins
     if (!gr || (c->n_curves > 0 && !gr->d_gauss)) return BZ_ERR_ARG;
     if ((st = bz_render_bwd_gauss(g, b, o, d_image, state, gr->d_gauss, s)) != BZ_OK) return st;
     return bz_render_bwd_curves(c, o, gr->d_gauss, gr, s);
+}
+
+bz_status bz_bwd_scratch_size(int64_t n_gauss, int64_t *bytes) {
+    if (n_gauss < 0 || !bytes) return BZ_ERR_ARG;
+    *bytes = (int64_t)sizeof(float) * kGradPlanes * (n_gauss > 0 ? n_gauss : 1);
+    return BZ_OK;
+}
+
+bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
+                                const bz_opts *o, const float *d_image, const bz_pixstate *state,
+                                bz_grads *gr, float *scratch, int64_t scratch_bytes,
+                                hipStream_t s) {
+    bz_status st = check_opts(o);
+    if (st != BZ_OK) return st;
+    if ((st = check_curves(c)) != BZ_OK) return st;
+    if (!g || g->n != c->n_gauss) return BZ_ERR_ARG;
+    if (!gr || (c->n_curves > 0 && !gr->d_gauss)) return BZ_ERR_ARG;
+    if ((st = check_bwd_gauss(g, b, o, d_image, state, gr->d_gauss)) != BZ_OK) return st;
+    if ((st = check_bwd_curves(c, o, gr->d_gauss, gr)) != BZ_OK) return st;
+    if (c->n_gauss > 0 && (!scratch || scratch == gr->d_gauss)) return BZ_ERR_ARG;
+    int64_t need = 0;
+    if ((st = bz_bwd_scratch_size(c->n_gauss, &need)) != BZ_OK) return st;
+    if (c->n_gauss > 0 && scratch_bytes < need) return BZ_ERR_CAPACITY;
+    (void)hipGetLastError();
+    st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s));
+    if (st != BZ_OK) return st;
+    return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
 }
 
 bz_status bz_curve_area(const bz_curves *c, float *area, hipStream_t s) {

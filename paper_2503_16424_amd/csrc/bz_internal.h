@@ -90,14 +90,17 @@ struct L2Out {
     float scale;
 };
 // st == nullptr: the forward writes only the image; the backward recomputes
-// the blend state per tile.  l2 == nullptr: no loss gradient.
+// the blend state per tile.  l2 == nullptr: no loss gradient.  packed: d_gauss
+// holds 9 floats per Gaussian instead of 9 planes.
 hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, float *image,
                       const bz_pixstate *st, const L2Out *l2, hipStream_t s);
 hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
                             const bz_opts &o, const float *d_image, const bz_pixstate *st,
-                            float *d_gauss, hipStream_t s);
+                            float *d_gauss, bool packed, hipStream_t s);
+// planes non-null: d_gauss is packed (9 floats per Gaussian) and the planes are
+// written too.
 hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,
-                             const bz_grads &gr, hipStream_t s);
+                             float *planes, const bz_grads &gr, hipStream_t s);
 hipError_t launch_l2(const float *image, const float *target, int64_t n, float scale,
                      float *d_image, float *loss, hipStream_t s);
 hipError_t launch_area(const bz_curves &c, float *area, hipStream_t s);

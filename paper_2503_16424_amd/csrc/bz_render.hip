@@ -26,6 +26,8 @@
 // threads for curves of at most 64 Gaussians, 256 for larger ones; no
 // atomics): it chains the per-Gaussian gradients through the sampling of
 // Sec. 3.3.
+#include <cstddef>
+
 #include "bz_geom.h"
 
 namespace bz {
@@ -100,7 +102,8 @@ struct TileArgs {
     int tab_cap;              // positions of the backward's per-tile sum table
     // backward
     const float *d_image;
-    float *d_gauss;
+    float *d_gauss;           // 9 planes of n_gauss, or (packed) 9 floats per Gaussian
+    bool packed;
     int64_t n_gauss;
     // forward with the L2 loss gradient: target, d_image out, loss sum, scale
     const float *l2_target;
@@ -550,100 +553,93 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     }
 }
 
-// Broadcast lane 0's 64-bit value as a wave-uniform (scalar) value.  The
-// builtin returns a signed int: each half goes through uint32_t so that the
-// low half is zero-extended, not sign-extended into the high word.
-__device__ inline uint64_t uniform_u64(uint64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+// A lane's 64-bit value as a wave-uniform (scalar) one.  The builtin returns a
+// signed int: each half goes through uint32_t so that the low half is
+// zero-extended, not sign-extended into the high word.
+__device__ inline uint64_t lane_u64(uint64_t v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
     return ((uint64_t)hi << 32) | (uint64_t)lo;
 }
 
-template <int CTRL>
-__device__ inline float dpp_f(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
-                                                                 CTRL, 0xF, 0xF, false));
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+// Inclusive scans over the 16 lanes of each row, of 4 registers at once: four
+// DPP row shifts, in place; a lane without a source is left as it is, which is
+// the identity for product and sum alike.  The steps of the four registers
+// alternate, so a DPP read comes three instructions after the write it
+// depends on (two are required); the leading s_nop covers the inputs.
+#define BZ_ROW_SCAN4(OP, v)                                                             \
+    asm("s_nop 1\n\t"                                                                   \
+        OP " %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %2, %2, %2 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %3, %3, %3 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %2, %2, %2 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %3, %3, %3 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %2, %2, %2 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %3, %3, %3 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %2, %2, %2 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"                       \
+        OP " %3, %3, %3 row_shr:8 row_mask:0xf bank_mask:0xf"                           \
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]))
+
+// v of the lane before in the row of 16; the row's first lane gets `first`.
+__device__ inline float row_shifted(float first, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(first), __float_as_int(v),
+                                                      0x111, 0xF, 0xF, false));
 }
 
-// Exchange lanes 32..63 of x[i] with lanes 0..31 of y[i] (v_permlane32_swap),
-// or the odd 16-lane rows of x[i] with the even rows of y[i]
-// (v_permlane16_swap), for 8 register pairs.  Both registers of a pair are
-// outputs of the instruction; the compiler builtins of this toolchain return
-// the first one twice, so the instructions are written here with both
-// operands read-write.  One s_nop 1 gives the two wait states a swap needs
-// after a VALU write of its operands; the 8 swaps of a group do not depend on
-// each other.
-#define BZ_SWAP8(OP, x, y, o)                                                           \
-    asm volatile("s_nop 1\n\t" OP " %0, %8\n\t" OP " %1, %9\n\t" OP " %2, %10\n\t" OP    \
-                 " %3, %11\n\t" OP " %4, %12\n\t" OP " %5, %13\n\t" OP " %6, %14\n\t" OP \
-                 " %7, %15"                                                             \
-                 : "+v"(x[o + 0]), "+v"(x[o + 1]), "+v"(x[o + 2]), "+v"(x[o + 3]),       \
-                   "+v"(x[o + 4]), "+v"(x[o + 5]), "+v"(x[o + 6]), "+v"(x[o + 7]),       \
-                   "+v"(y[o + 0]), "+v"(y[o + 1]), "+v"(y[o + 2]), "+v"(y[o + 3]),       \
-                   "+v"(y[o + 4]), "+v"(y[o + 5]), "+v"(y[o + 6]), "+v"(y[o + 7]))
-
-// d[i] on the lanes of the banks in MASK (4-lane groups of a 16-lane row) =
-// s[i] + s[i] read from the DPP partner lane (row_ror:8: lane ^ 8;
-// row_half_mirror: lane ^ 7 inside 8 lanes), for 4 registers; lanes of the
-// other banks keep d (OUT "+v") or are left undefined (OUT "=&v", early
-// clobber: the block reads its inputs after writing outputs).  The wait
-// states before the first DPP read of a freshly written register come first.
-#define BZ_DPPADD4(OUT, CTRL, MASK, d, s, od, os)                                        \
-    asm volatile("s_nop 1\n\t"                                                          \
-                 "v_add_f32_dpp %0, %4, %4 " CTRL " row_mask:0xf bank_mask:" MASK "\n\t"  \
-                 "v_add_f32_dpp %1, %5, %5 " CTRL " row_mask:0xf bank_mask:" MASK "\n\t"  \
-                 "v_add_f32_dpp %2, %6, %6 " CTRL " row_mask:0xf bank_mask:" MASK "\n\t"  \
-                 "v_add_f32_dpp %3, %7, %7 " CTRL " row_mask:0xf bank_mask:" MASK          \
-                 : OUT(d[od + 0]), OUT(d[od + 1]), OUT(d[od + 2]), OUT(d[od + 3])        \
-                 : "v"(s[os + 0]), "v"(s[os + 1]), "v"(s[os + 2]), "v"(s[os + 3]))
-
-// d[i] (2 registers) on the banks in MASK = s[i] + s[i] of the DPP partner.
-#define BZ_DPPADD2(OUT, CTRL, MASK, d, s, od, os)                                        \
-    asm volatile("s_nop 1\n\t"                                                          \
-                 "v_add_f32_dpp %0, %2, %2 " CTRL " row_mask:0xf bank_mask:" MASK "\n\t"  \
-                 "v_add_f32_dpp %1, %3, %3 " CTRL " row_mask:0xf bank_mask:" MASK          \
-                 : OUT(d[od + 0]), OUT(d[od + 1])                                        \
-                 : "v"(s[os + 0]), "v"(s[os + 1]))
-
-// Transposed reduction of 32 per-lane values over the 64 lanes: on return
-// lanes 2i and 2i + 1 both hold the sum over all lanes of v[i].  Each level
-// halves the values a lane holds by exchanging half of them with a partner
-// lane: lanes l and l^32 (permlane32 swap), l^16 (permlane16 swap), l^8 (DPP
-// row rotate by 8), l^7 (DPP half-row mirror), l^3 (DPP quad permute); bit b
-// of the lane index decides which half a lane keeps, so after five levels
-// lanes 2i and 2i + 1 hold index i, and a last DPP add over l^1 completes the
-// sum.  Lanes l and l^8 differ in bit 1 of their bank, lanes l and l^7 in bit
-// 0, so those two levels are pairs of bank-masked DPP adds (the lanes of a
-// bank add the index they keep).  Works in place: v holds partial sums
-// afterwards.
-__device__ inline float reduce_scatter32(float (&v)[32], int lane) {
-    BZ_SWAP8("v_permlane32_swap_b32", v, (v + 16), 0);
-    BZ_SWAP8("v_permlane32_swap_b32", v, (v + 16), 8);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] += v[i + 16];
-    BZ_SWAP8("v_permlane16_swap_b32", v, (v + 8), 0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] += v[i + 8];
-    float w[4];
-    BZ_DPPADD4("=&v", "row_ror:8", "0x3", w, v, 0, 0);
-    BZ_DPPADD4("+v", "row_ror:8", "0xc", w, v, 0, 4);
-    float u[2];
-    BZ_DPPADD2("=&v", "row_half_mirror", "0x5", u, w, 0, 0);
-    BZ_DPPADD2("+v", "row_half_mirror", "0xa", u, w, 0, 2);
-    const bool b1 = lane & 2;
-    const float keep = b1 ? u[1] : u[0], send = b1 ? u[0] : u[1];
-    const float r = keep + dpp_f<0x1B>(send);      // quad_perm [3,2,1,0] (lane ^ 3)
-    return r + dpp_f<0xB1>(r);                     // quad_perm [1,0,3,2] (lane ^ 1)
+// A constant or wave-uniform float in a vector register: an FMA, add or
+// multiply with an operand in a scalar register takes 4 cycles on this part,
+// with all operands in vector registers (or inline constants) 2.5.
+__device__ inline float vector_f32(float v) {
+    float r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+    return r;
 }
 
-// Gaussians per reduction batch: 3 x 10 = 30 sums in 32 registers.  (Seven
-// Gaussians in 64 registers cost fewer reduction instructions per sum, but the
-// kernel then needs 96 registers and spills; the reverse pass waits on memory
-// more than it issues arithmetic, and the smaller form, with more waves and no
-// spills, runs it 30% faster.)
-constexpr int kSlots = 3;
-constexpr int kAcc = 32;
-constexpr int kSums = 10;     // per-lane values of one Gaussian
+// min(a, b) of finite values, both in vector registers, as one instruction
+// (fminf canonicalises its operands first).
+__device__ inline float min_f32(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The reverse pass of one wave (an 8x8 quad, 64 pixels) takes 16 list entries
+// ("slots") at a time.  Lane (q = l / 16, j = l mod 16) works on slot j and a
+// quarter of the pixels: register r of block b = 0..3 is pixel 16 b + 4 q + r
+// of the quad (row-major), so x = 4 (q & 1) + r and y = 2 b + (q >> 1).
+//  - T and the sum behind run over the slots as scans across the 16 lanes of a
+//    row; everything else of a (pixel, slot) is independent.
+//  - A slot's sums over the quad's pixels are sums over a lane's own 16
+//    registers (moments in r and b, whose factors are constants) and then over
+//    four lanes, where one lane per pixel needs a reduction over 64 lanes for
+//    each slot (100 of 287 cycles a slot in that form).
+constexpr int kGroup = 16;
+// Staged rows of a slot: -u0, e'.x, e'.y | -w0, -f.y, f.x | r, g, b | o', -o' g_min
+constexpr int kStageRows = 11;
+
+// A wave's LDS.  The recomputing form's front-to-back sweep stages its 64
+// records (3072 bytes) over rec and pos before they are in use.
+struct __align__(16) BwdWave {
+    float rec[kStageRows][64];   // staged slots
+    uint32_t pos[128];           // list positions waiting, descending; the first 64 staged
+    uint32_t nl[64];             // per pixel: bound on its contributors' positions
+    float g[3][64];              // image gradient
+    // per pixel, in front of the slots taken so far: transmittance, and the sum
+    // of alpha T (c . g) behind
+    float T[64], H[64];
+};
+static_assert(offsetof(BwdWave, nl) >= 64 * sizeof(Staged), "sweep overlay");
+
+constexpr int kSums = 10;     // sums over pixels of one Gaussian
 
 // What a Gaussian's sums hold.  With f the alpha gradient, o' the scaled
 // opacity, G = 2^-p2, p2 = u^2 + w^2 (u = e' . d, w = f x d, d = pixel - mean)
@@ -653,57 +649,257 @@ constexpr int kSums = 10;     // per-lane values of one Gaussian
 //     A = e'.x^2 + f.y^2, B = e'.x e'.y - f.x f.y, C = e'.y^2 + f.x^2;
 //   dL/dQ = -P (dx^2 / 2, dx dy, dy^2 / 2);  dL/do = f (G - g_min) / (1 - g_min);
 //   dL/dcolour = alpha T g.
-// Entries in the tile's LDS table add moments about the tile centre: with
-// (x, y) the pixel centre relative to it, sums 0-9 are f G (1, x, y, x^2, x y,
-// y^2), alpha T g (3) and f; the table's flush turns them into the planes with
-// the record's mean and shape (sum(f G dx) = sum(f G x) - mx sum(f G), ...),
-// which per pixel costs five products instead of eleven.  Entries past the
-// table add the nine plane values directly (sums 0-8, the constant factors
-// below applied after the reduction).
-__device__ inline float plane_scale(int v, float inv_1mg) {
-    return v < 2 ? 1.38629436112f : v == 3 ? -1.f : (v == 2 || v == 4) ? -0.5f : v == 5 ? inv_1mg : 1.f;
+// The sums are moments about the tile centre: with (x, y) the pixel centre
+// relative to it, sums 0-9 are f G (1, x, y, x^2, xy, y^2), alpha T g (3) and
+// f; planes_of turns them into the planes with the record's mean and shape
+// (sum(f G dx) = sum(f G x) - mx sum(f G), ...).
+__device__ inline void planes_of(const TileArgs &a, uint32_t id, const float (&S)[kSums], float ox,
+                                 float oy, float (&out)[kGradPlanes]) {
+    const float4 m = a.rec[3 * (int64_t)id];
+    const float4 q = a.rec[3 * (int64_t)id + 1];
+    const float mx = (m.x - ox) + m.z, my = (m.y - oy) + m.w;   // mean - tile centre
+    const float ex = kHalfLog2eSqrt * q.x, ey = kHalfLog2eSqrt * q.y;
+    const float fx = q.z * ex, fy = q.z * ey;
+    const float op = q.w * a.inv_1mg;
+    // sums of f G (dx, dy, dx^2, dx dy, dy^2), d = pixel - mean
+    const float sx = fmaf(-mx, S[0], S[1]), sy = fmaf(-my, S[0], S[2]);
+    const float sxx = fmaf(-mx, S[1] + sx, S[3]);
+    const float sxy = fmaf(-mx, sy, fmaf(-my, S[1], S[4]));
+    const float syy = fmaf(-my, S[2] + sy, S[5]);
+    const float A = fmaf(ex, ex, fy * fy), B = fmaf(ex, ey, -fx * fy), C = fmaf(ey, ey, fx * fx);
+    const float k2 = 1.38629436112f * op;        // 2 ln 2 o'
+    out[0] = k2 * fmaf(A, sx, B * sy);
+    out[1] = k2 * fmaf(B, sx, C * sy);
+    out[2] = -0.5f * op * sxx;
+    out[3] = -op * sxy;
+    out[4] = -0.5f * op * syy;
+    out[5] = fmaf(-a.g_min, S[9], S[0]) * a.inv_1mg;
+    out[6] = S[6];
+    out[7] = S[7];
+    out[8] = S[8];
 }
 
-// Tile-list positions pooled in LDS by the backward.  With 16x16 tiles a
-// block then takes 256 x 48 B of staging + 10 x 352 x 4 B of sums = 25.8 KiB,
-// so six blocks share a CU's 160 KiB of LDS.  (Five blocks ran 5% slower; with
-// half the positions more sums go to global atomics, 16% slower; a table sized
-// to each tile shape's occupancy ran 8x8 and 16x8 tiles 4-9% slower and 16x32
-// tiles 12% slower.)  The recomputing backward also keeps its batch masks in
-// LDS; its table gives up their bytes (table_cap), so both forms hold the
-// same LDS per block: 240 positions at 16x16, 6% faster than 352 at five
-// blocks per CU.
-constexpr int kTableCap = 352;
+// Add the nine values of up to n (<= 64) Gaussians to d_gauss: val[v][.] and
+// the Gaussian ids (kNoGauss: none) in the wave's LDS, one Gaussian per column.
+// Float atomics at device scope pass the L2 (its eight copies are one per XCD)
+// and go to memory one 64-byte line per request, at about 20 G requests/s
+// however few of a line's floats they touch.  In the packed form consecutive
+// lanes take consecutive values of a Gaussian, so that a Gaussian costs one or
+// two requests instead of nine: on the 2048x2048 frame 16.9 M requests a launch
+// (0.82 ms of them alone) became 6.5 M.
+constexpr uint32_t kNoGauss = 0xffffffffu;
+__device__ inline void add_grads(const TileArgs &a, const float *val, int pitch,
+                                 const uint32_t *ids, int n, int lane) {
+    if (a.packed) {
+        int e = lane / kGradPlanes, v = lane - e * kGradPlanes;
+        for (int i = lane; i < kGradPlanes * n; i += 64) {
+            const uint32_t id = ids[e];
+            const float x = val[v * pitch + e];
+            if (id != kNoGauss && x != 0.f) atomicAdd(a.d_gauss + (int64_t)id * kGradPlanes + v, x);
+            e += 7;                              // 64 = 7 * 9 + 1
+            if (++v == kGradPlanes) {
+                v = 0;
+                ++e;
+            }
+        }
+    } else if (lane < n && ids[lane] != kNoGauss) {
+#pragma unroll
+        for (int v = 0; v < kGradPlanes; ++v) {
+            const float x = val[v * pitch + lane];
+            if (x != 0.f) atomicAdd(a.d_gauss + (int64_t)v * a.n_gauss + ids[lane], x);
+        }
+    }
+}
+
+// Tile-list positions pooled in LDS by the backward, as doubles: an LDS float
+// atomic takes 2.8 CU cycles for every lane (177 for a full wave, whatever the
+// addresses), a double one 8 for the whole wave.  With 16x16 tiles a block takes
+// 4 x 4.8 KiB for its waves and 10 x 258 x 8 B of sums = 39.2 KiB, so four blocks
+// (the four waves per SIMD its registers allow) share a CU's 160 KiB of LDS; 128
+// positions ran 5% slower on the 2048x2048 frame, 160 at five waves per SIMD 25%
+// (the registers spill).  The recomputing backward also keeps its batch masks in
+// LDS; its table gives up their bytes (table_cap), so both forms hold the same
+// LDS per block.
+constexpr int kTableCap = 256;
+constexpr int kTabPad = 2;
 
 // Backward stage 1.  Each wave walks its tile list from the last entry any of
-// its pixels used down to the first.  Per pixel and contributor (reverse
-// order): T before it = T after / (1 - alpha); colour gradient alpha T g;
-// alpha gradient T (c - A) . g with A the colour composited behind it (starts
-// at the background, A <- alpha c + (1 - alpha) A; only A . g is carried);
-// then, unless alpha was clamped, the opacity gradient and dL/dp = -alpha_bar
-// o' G, which gives the mean gradient -dL/dp Q d and the conic gradient dL/dp
-// (dx^2/2, dx dy, dy^2/2).  The per-lane values of three Gaussians are summed
-// over the wave in one transposed reduction and added, with one atomic
-// instruction, to the tile's LDS sum table (positions below its capacity) or
-// straight to the per-Gaussian planes in HBM; the table is added to the planes
-// when the tile is done.
+// its pixels used down to the first, over the entries the forward marked (at
+// least one pixel of the quad used them).  Per pixel and contributor, in
+// reverse order: T before it = T after / (1 - alpha); colour gradient alpha T
+// g; with H the sum of alpha T (c . g) over everything behind it (the
+// background first), alpha gradient = T (c . g) - H / (1 - alpha); then, unless
+// alpha was clamped, the opacity gradient and dL/dp = -alpha_bar o' G.  The
+// marked entries are compacted into a queue of list positions, staged 64 at a
+// time and taken 16 at a time; the sums of 16 entries go, one LDS atomic per
+// sum, to the tile's table (positions below its capacity) or straight to the
+// per-Gaussian planes in HBM; the table is added to the planes when the tile
+// is done.
 //
 // kRecompute: the blend state (T after the last contributor, the bound on its position and
 // the per-batch contribution masks) is not read from memory but recomputed by
 // a front-to-back sweep of the same quad (colour omitted), with the
 // instruction sequence of the forward pass, so T and the positions are those
 // the forward pass had.  The masks of the first kVisCap batches stay in LDS;
-// later batches are staged whole and box-tested again (a superset of the
-// contributors: the others add exact zeros).
+// later batches are box-tested again (a superset of the contributors: the
+// others add exact zeros).
 constexpr int kVisCap = 128;
+
+// Lane constants of the reverse pass: the lane's pixel centres relative to the
+// tile centre (x of register r, y of block b), and constants kept in vector
+// registers.
+struct BwdLane {
+    float x[4], y[4], g_min, amax, three, nine;
+};
+
+// One group of 16 staged slots against the quad's 64 pixels; s: this lane's
+// slot, last: the lane of the row's last slot.  check: some slot of the group may
+// lie at or past a pixel's bound.  Returns three sums of slot j: q = 0: 0, 1, 2;
+// q = 1: 3, 4; q = 2: 5, 6, 7; q = 3: 8, 9.
+// u, w, G and alpha take the operations of the front-to-back sweep in its order
+// (one rounding more or less can turn the decision whether alpha is clamped,
+// where the gradient jumps).
+__device__ inline void bwd_group(BwdWave &wl, int s, int q, bool last, bool check,
+                                 const BwdLane &L, float (&out)[3]) {
+    const float nu0 = wl.rec[0][s], ex = wl.rec[1][s], ey = wl.rec[2][s];
+    const float nw0 = wl.rec[3][s], mfy = wl.rec[4][s], fx = wl.rec[5][s];
+    const float cr = wl.rec[6][s], cgr = wl.rec[7][s], cb = wl.rec[8][s];
+    const float op = wl.rec[9][s], mog = wl.rec[10][s];
+    const uint32_t pos = wl.pos[s];
+    float wx[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) wx[r] = fmaf(mfy, L.x[r], nw0);
+    // sums over the lane's pixels: f G (1, r, r^2, b, r b, b^2), f, alpha T g
+    float S0 = 0.f, Sr = 0.f, Srr = 0.f, Sb = 0.f, Srb = 0.f, Sbb = 0.f, Sf = 0.f;
+    float Sc0 = 0.f, Sc1 = 0.f, Sc2 = 0.f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int p4 = 16 * b + 4 * q;
+        const floatx4 g0 = *reinterpret_cast<const floatx4 *>(&wl.g[0][p4]);
+        const floatx4 g1 = *reinterpret_cast<const floatx4 *>(&wl.g[1][p4]);
+        const floatx4 g2 = *reinterpret_cast<const floatx4 *>(&wl.g[2][p4]);
+        const floatx4 T = *reinterpret_cast<const floatx4 *>(&wl.T[p4]);
+        const floatx4 H = *reinterpret_cast<const floatx4 *>(&wl.H[p4]);
+        float G[4], al[4], rho[4], Tb[4], Hb[4], x[4], cg[4], f[4];
+        bool shaped[4];
+        const float uy = fmaf(ey, L.y[b], nu0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float u = fmaf(ex, L.x[r], uy), w = fmaf(fx, L.y[b], wx[r]);
+            G[r] = __builtin_amdgcn_exp2f(-fmaf(u, u, w * w));
+        }
+        if (check) {                         // wave-uniform
+            const uint4 n4 = *reinterpret_cast<const uint4 *>(&wl.nl[p4]);
+            G[0] = pos < n4.x ? G[0] : 0.f;
+            G[1] = pos < n4.y ? G[1] : 0.f;
+            G[2] = pos < n4.z ? G[2] : 0.f;
+            G[3] = pos < n4.w ? G[3] : 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float araw = fmaf(op, G[r], mog);
+            const bool c = G[r] > L.g_min;            // contributes
+            shaped[r] = c && araw <= L.amax;          // and alpha is not clamped
+            const float acl = min_f32(araw, L.amax);
+            al[r] = c ? acl : 0.f;
+            rho[r] = __builtin_amdgcn_rcpf(1.f - al[r]);
+            Tb[r] = rho[r];
+            cg[r] = fmaf(cr, g0[r], fmaf(cgr, g1[r], cb * g2[r]));
+        }
+        BZ_ROW_SCAN4("v_mul_f32_dpp", Tb);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            Tb[r] *= T[r];                            // T before the slot
+            al[r] *= Tb[r];                           // its weight alpha T
+            x[r] = al[r] * cg[r];
+            Sc0 = fmaf(al[r], g0[r], Sc0);
+            Sc1 = fmaf(al[r], g1[r], Sc1);
+            Sc2 = fmaf(al[r], g2[r], Sc2);
+            Hb[r] = row_shifted(H[r], x[r]);
+        }
+        BZ_ROW_SCAN4("v_add_f32_dpp", Hb);            // the sum behind the slot
+        if (last) {
+            *reinterpret_cast<floatx4 *>(&wl.T[p4]) = floatx4{Tb[0], Tb[1], Tb[2], Tb[3]};
+            *reinterpret_cast<floatx4 *>(&wl.H[p4]) =
+                floatx4{Hb[0] + x[0], Hb[1] + x[1], Hb[2] + x[2], Hb[3] + x[3]};
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // T (c . g) - H / (1 - alpha).  The slot's own term stays out of H: at
+            // alpha near 1 two terms that both hold it would nearly cancel.
+            const float ab = fmaf(Tb[r], cg[r], -rho[r] * Hb[r]);
+            f[r] = shaped[r] ? ab : 0.f;
+            Sf += f[r];
+            f[r] *= G[r];
+        }
+        const float R = (f[0] + f[1]) + (f[2] + f[3]);
+        const float X = fmaf(f[3], L.three, fmaf(f[2], 2.f, f[1]));
+        const float XX = fmaf(f[3], L.nine, fmaf(f[2], 4.f, f[1]));
+        S0 += R;
+        Sr += X;
+        Srr += XX;
+        if (b == 1) {
+            Sb += R;
+            Srb += X;
+            Sbb += R;
+        } else if (b > 1) {
+            const float fb = b == 2 ? 2.f : L.three;
+            Sb = fmaf(R, fb, Sb);
+            Srb = fmaf(X, fb, Srb);
+            Sbb = fmaf(R, b == 2 ? 4.f : L.nine, Sbb);
+        }
+        // The block's sums are finished here: left to the compiler they sink
+        // past the next blocks' branches, with every factor of theirs kept
+        // until then, and spill.
+        asm volatile("" : "+v"(S0), "+v"(Sr), "+v"(Srr), "+v"(Sb), "+v"(Srb), "+v"(Sbb), "+v"(Sf),
+                     "+v"(Sc0), "+v"(Sc1), "+v"(Sc2));
+    }
+    // moments about the tile centre: x = x[0] + r, y = y[0] + 2 b
+    const float X0 = L.x[0], Y0 = L.y[0];
+    float v[10];
+    v[0] = S0;
+    v[1] = fmaf(X0, S0, Sr);
+    v[2] = fmaf(Sb, 2.f, Y0 * S0);
+    v[3] = fmaf(X0, v[1] + Sr, Srr);
+    v[4] = fmaf(Y0, v[1], 2.f * fmaf(X0, Sb, Srb));
+    v[5] = fmaf(Y0, fmaf(Sb, 2.f, v[2]), 4.f * Sbb);
+    v[6] = Sc0;
+    v[7] = Sc1;
+    v[8] = Sc2;
+    v[9] = Sf;
+    // over the four lanes of the slot: halves exchanged with lane l ^ 32, then
+    // thirds with lane l ^ 16
+    float y[5], z[3];
+    asm("s_nop 1\n\t"
+        "v_permlane32_swap_b32 %0, %5\n\t"
+        "v_permlane32_swap_b32 %1, %6\n\t"
+        "v_permlane32_swap_b32 %2, %7\n\t"
+        "v_permlane32_swap_b32 %3, %8\n\t"
+        "v_permlane32_swap_b32 %4, %9"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+          "+v"(v[7]), "+v"(v[8]), "+v"(v[9]));
+#pragma unroll
+    for (int i = 0; i < 5; ++i) y[i] = v[i] + v[i + 5];
+    float pad = 0.f;
+    asm("s_nop 1\n\t"
+        "v_permlane16_swap_b32 %0, %3\n\t"
+        "v_permlane16_swap_b32 %1, %4\n\t"
+        "v_permlane16_swap_b32 %2, %5"
+        : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]), "+v"(y[4]), "+v"(pad));
+    z[0] = y[0] + y[3];
+    z[1] = y[1] + y[4];
+    z[2] = y[2] + pad;
+    out[0] = z[0];
+    out[1] = z[1];
+    out[2] = z[2];
+}
 
 template <bool kRecompute>
 __device__ inline void bwd_tile(const TileArgs &a, int tile) {
-    // dynamic LDS: [waves][64] staged records, the sum table, and (kRecompute)
+    // dynamic LDS: per wave a BwdWave, the sum table, and (kRecompute)
     // [waves][kVisCap] batch masks
-    extern __shared__ Staged s_stage[];
+    extern __shared__ __align__(16) unsigned char s_bwd[];
     __shared__ uint32_t s_top[16];
-    __shared__ float s_q0[16][2];      // the tile centre (same for every wave), read when staging
     const int nwaves = blockDim.x >> 6;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -716,63 +912,55 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
     const float lx = (float)(lane & 7), ly = (float)(lane >> 3);   // pixel - first pixel of the quad
     const float qx0 = (float)x0 + 0.5f, qy0 = (float)y0 + 0.5f;
     // The reverse pass measures from the tile centre (ox, oy): the moments the
-    // quads of a tile add to one table need one origin.  (cx, cy): this pixel's
-    // centre, (bx, by): the quad's first pixel centre, both relative to it.
+    // quads of a tile add to one table need one origin.  (bx, by): the quad's
+    // first pixel centre relative to it.
     const float ox = (float)(tg.tx * a.tile_w) + 0.5f * (float)a.tile_w;
     const float oy = (float)(tg.ty * a.tile_h) + 0.5f * (float)a.tile_h;
     const float bx = qx0 - ox, by = qy0 - oy;
-    const float cx = bx + lx, cy = by + ly;
-    if (lane == 0) {
-        s_q0[w][0] = ox;
-        s_q0[w][1] = oy;
-    }
-    Staged *my = s_stage + w * 64;
-    // LDS offset of the slice (the recomputing form, short of registers,
-    // leaves its address arithmetic to the compiler)
-    const uint32_t my_off = kRecompute ? (uint32_t)(uintptr_t)my
-                                       : vector_copy((uint32_t)(uintptr_t)my);
-    // Per-tile sums, plane-major [kSums][tab_cap], indexed by tile-list position:
-    // the quads of a tile share most of their Gaussians, so their sums meet
-    // here and leave the block with one global atomic per (Gaussian, plane).
-    const int tab_cap = a.tab_cap;
-    float *table = reinterpret_cast<float *>(s_stage + nwaves * 64);
+    BwdWave &wl = reinterpret_cast<BwdWave *>(s_bwd)[w];
+    // Per-tile sums, plane-major [kSums][tab_cap + kTabPad], indexed by
+    // tile-list position: the quads of a tile share most of their Gaussians, so
+    // their sums meet here and leave the block with one global atomic per
+    // (Gaussian, plane).
+    const int tab_cap = a.tab_cap, tab_p = tab_cap + kTabPad;
+    double *table = reinterpret_cast<double *>(s_bwd + (size_t)nwaves * sizeof(BwdWave));
     // kRecompute: per-wave batch masks after the table
-    uint64_t *s_vis = reinterpret_cast<uint64_t *>(table + kSums * tab_cap) + w * kVisCap;
+    uint64_t *s_vis = reinterpret_cast<uint64_t *>(table + kSums * tab_p) + w * kVisCap;
 
-    const uint32_t start = a.ranges[2 * tile];
-    const uint32_t len = a.ranges[2 * tile + 1] - start;
+    // wave-uniform: held in scalar registers
+    const uint32_t start = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ranges[2 * tile]);
+    const uint32_t len =
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ranges[2 * tile + 1]) - start;
     const uint64_t *vis =
         kRecompute ? nullptr : a.visit + (int64_t)w * a.words_per_plane + visit_word(start, tile);
     const int64_t pix = tg.pix0 + (int64_t)y * tg.W + x;
     const int64_t plane = (int64_t)tg.W * tg.H;
     const float *dimg = a.d_image + 2 * tg.pix0;   // canvas planes from 3 * pix0
     uint32_t nl = 0;
-    float T = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+    float Tf = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
     if (kRecompute) {
         if (wave_on) {
+            Staged *my = reinterpret_cast<Staged *>(&wl);
             const Sweep r = fwd_sweep<false, false>(a, my, start, start + len, lx, ly, qx0, qy0,
                                                     valid, lane, [&](uint32_t k, uint64_t bits) {
                                                         if (lane == 0 && k < kVisCap) s_vis[k] = bits;
                                                     });
             nl = valid ? r.last : 0u;
-            T = valid ? r.T : 0.f;
+            Tf = valid ? r.T : 0.f;
         }
         wave_lds_sync();
     } else if (valid) {
         nl = a.n_last[pix];
-        T = a.t_final[pix];
+        Tf = a.t_final[pix];
     }
     if (valid) {
         g0 = dimg[pix];
         g1 = dimg[plane + pix];
         g2 = dimg[2 * plane + pix];
     }
-    // A (the colour composited behind, from the background forward) enters the
-    // gradient only through A . g, so that scalar is what the pass carries:
-    // A <- alpha c + (1 - alpha) A gives A.g <- alpha (c.g) + (1 - alpha) A.g.
-    float Ag = fmaf(tg.bg0, g0, fmaf(tg.bg1, g1, tg.bg2 * g2));
     uint32_t top = wave_max_u32(nl);   // wave-uniform
     top = top < len ? top : len;
+    const uint32_t min_nl = wave_min_u32(valid ? nl : 0xffffffffu);
     if (lane == 0) s_top[w] = top;
     __syncthreads();
     uint32_t top_block = 0;
@@ -780,203 +968,185 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
     const int tab_n = (int)(top_block < (uint32_t)tab_cap ? top_block : (uint32_t)tab_cap);
     for (int i = threadIdx.x; i < kSums * tab_n; i += blockDim.x) {
         const int v = i / tab_n;
-        table[v * tab_cap + (i - v * tab_n)] = 0.f;
+        table[v * tab_p + (i - v * tab_n)] = 0.0;
     }
-    __syncthreads();
-
-    const float g_min = a.g_min, amax = a.alpha_max, inv_1mg = a.inv_1mg;
-    const int64_t ng = a.n_gauss;
-    // sum index of this lane after the reduction (lanes 2i and 2i + 1 hold
-    // sum i; the even one stores it)
-    const int my_o = lane >> 1;
-    const bool my_store = (lane & 1) == 0;
-    const int my_v = my_o % kSums, my_s = my_o / kSums;
-    uint32_t slot_pos[kSlots];
+    // the quad's pixels into LDS, and from there into the lanes of the products
+    const int q = lane >> 4, j = lane & 15;
+    {
+        wl.g[0][lane] = g0;
+        wl.g[1][lane] = g1;
+        wl.g[2][lane] = g2;
+        wl.nl[lane] = nl;
+        wl.T[lane] = Tf;
+        // behind everything: the background
+        wl.H[lane] = Tf * fmaf(tg.bg0, g0, fmaf(tg.bg1, g1, tg.bg2 * g2));
+    }
+    BwdLane L = {{}, {}, vector_f32(a.g_min), vector_f32(a.alpha_max), vector_f32(3.f),
+                 vector_f32(9.f)};
 #pragma unroll
-    for (int i = 0; i < kSlots; ++i) slot_pos[i] = 0;
+    for (int i = 0; i < 4; ++i) {
+        L.x[i] = bx + (float)(4 * (q & 1) + i);
+        L.y[i] = by + (float)((q >> 1) + 2 * i);
+    }
+    // the lane's sums of a group: nv of them from v0
+    const int v0 = q < 2 ? 3 * q : 3 * q - 1, nv = q & 1 ? 2 : 3;
+    __syncthreads();                                       // the table is clear
 
-    // Batches are visited last to first; inside a batch, entries from the
-    // highest position down.  Only entries whose bit the forward pass set (at
-    // least one pixel of this quad used them) are staged and visited.
-    // batch counter (32-bit: its test k > 0 runs on the scalar unit every slot)
-    int32_t k = wave_on ? (int32_t)(((uint64_t)top + 63) / 64) : 0;
-    uint64_t mask = 0;
-    uint32_t lo = 0;
-
-    // Slots not refilled in a round only feed sums that are never stored.
-    float acc[kAcc];
-#pragma unroll
-    for (int i = 0; i < kAcc; ++i) acc[i] = 0.f;
+    // Marked entries, last to first, into the queue of list positions: batch
+    // masks 64 at a time (lane l holds that of batch wtop - 1 - l), the ones
+    // with entries one by one.
+    const uint32_t nb = wave_on ? (uint32_t)(((uint64_t)top + 63) / 64) : 0u;
+    uint32_t kbox = nb;                                    // kRecompute: batches to box-test
+    uint32_t wtop = 0, wnext = kRecompute && nb > kVisCap ? kVisCap : nb;
+    uint64_t words = 0, nz = 0;
+    int qn = 0;
+    auto push = [&](uint32_t k, uint64_t word) {           // wave-uniform word of batch k
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0u));
+        const int n = __popcll(word);
+        if ((word >> lane) & 1ull) wl.pos[qn + n - 1 - (int)below] = 64 * k + (uint32_t)lane;
+        qn += n;
+    };
+    // only entries of this tile's list can be visited
+    auto in_list = [&](uint32_t k) {
+        const uint32_t avail = len - 64 * k;
+        return avail >= 64 ? ~0ull : ((1ull << avail) - 1ull);
+    };
     while (true) {
-        int filled = 0;
+        while (qn < 64) {
+            if (kRecompute && kbox > kVisCap) {
+                --kbox;
+                const uint32_t p = 64 * kbox + (uint32_t)lane;
+                bool hit = false;
+                if (p < len) {
+                    Staged st;
+                    hit = stage_entry_bwd(a, a.ids[start + p], ox, oy, bx, by, st);
+                }
+                push(kbox, __ballot(hit));
+                continue;
+            }
+            if (nz == 0) {
+                if (wnext == 0) break;
+                wtop = wnext;
+                wnext = wtop > 64 ? wtop - 64 : 0;
+                words = 0;
+                if ((uint32_t)lane < wtop) {
+                    const uint32_t k = wtop - 1 - (uint32_t)lane;
+                    words = (kRecompute ? s_vis[k] : vis[k]) & in_list(k);
+                }
+                nz = __ballot(words != 0);
+                continue;
+            }
+            const int i = __builtin_ctzll(nz);
+            nz &= nz - 1;
+            push(wtop - 1 - (uint32_t)i, lane_u64(words, i));
+        }
+        if (qn == 0) break;
+        const int n = qn < 64 ? qn : 64;
+        wave_lds_sync();
+        // stage the first n: lane l slot l, the slots past them contribute nothing
+        {
+            float4 sm = make_float4(0.f, 0.f, 0.f, 0.f), sq = sm, sc = sm;
+            if (lane < n) {
+                Staged st;
+                float4 shape;
+                stage_record<true>(a, a.ids[start + wl.pos[lane]], ox, oy, st, shape);
+                sm = st.m;
+                sq = st.q;
+                sc = st.c;
+            }
+            wl.rec[0][lane] = sm.x;
+            wl.rec[1][lane] = sm.z;
+            wl.rec[2][lane] = sm.w;
+            wl.rec[3][lane] = sm.y;
+            wl.rec[4][lane] = -sq.y;
+            wl.rec[5][lane] = sq.x;
+            wl.rec[6][lane] = sc.x;
+            wl.rec[7][lane] = sc.y;
+            wl.rec[8][lane] = sc.z;
+            wl.rec[9][lane] = sq.w;
+            wl.rec[10][lane] = -sc.w;
+        }
+        wave_lds_sync();
+        for (int s0 = 0; s0 < n; s0 += kGroup) {
+            const int s = s0 + j;
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)wl.pos[s0]);
+            float E[3];
+            bwd_group(wl, s, q, j == kGroup - 1, first >= min_nl, L, E);
+            const bool live = s < n;
+            const uint32_t p = live ? wl.pos[s] : 0u;
+            if (live && p < (uint32_t)tab_cap) {
+                double *row = table + v0 * tab_p + p;
+                atomicAdd(row, (double)E[0]);
+                atomicAdd(row + tab_p, (double)E[1]);
+                if (nv == 3) atomicAdd(row + 2 * tab_p, (double)E[2]);
+            }
+            if (first >= (uint32_t)tab_cap) {        // some lie past the table
+                wave_lds_sync();
+                wl.rec[v0][s] = E[0];
+                wl.rec[v0 + 1][s] = E[1];
+                if (nv == 3) wl.rec[v0 + 2][s] = E[2];
+                wave_lds_sync();
+                if (q == 0) {                        // the slot's own column, in place
+                    uint32_t id = kNoGauss;
+                    if (live && p >= (uint32_t)tab_cap) {
+                        float S[kSums], o[kGradPlanes];
 #pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
-            if (mask == 0) {
-                // the next batch with entries to visit, walking down
-                while (k > 0) {
-                    --k;
-                    lo = (uint32_t)k * 64;
-                    // only entries of this tile's list can be visited
-                    const uint32_t avail = len - lo;
-                    const uint64_t in_list = avail >= 64 ? ~0ull : ((1ull << avail) - 1ull);
-                    uint64_t vm;
-                    if (!kRecompute || k < kVisCap) {
-                        const uint64_t vraw = kRecompute ? s_vis[k] : vis[k];
-                        vm = uniform_u64(vraw) & in_list;
-                        if (vm != 0) {
-                            wave_lds_sync();
-                            if ((vm >> lane) & 1ull) {
-                                const uint32_t id = a.ids[start + lo + lane];
-                                Staged st;
-                                float4 q;
-                                const float *q0 = s_q0[w + opaque_zero()];
-                                stage_record<false>(a, id, q0[0], q0[1], st, q);
-                                my[lane] = st;
-                            }
-                            wave_lds_sync();
-                        }
-                    } else {
-                        wave_lds_sync();
-                        bool hit = false;
-                        if ((uint32_t)lane < avail) {
-                            const uint32_t id = a.ids[start + lo + lane];
-                            Staged st;
-                            const float *q0 = s_q0[w + opaque_zero()];
-                            hit = stage_entry_bwd(a, id, q0[0], q0[1], bx, by, st);
-                            my[lane] = st;
-                        }
-                        vm = __ballot(hit) & in_list;
-                        wave_lds_sync();
+                        for (int v = 0; v < kSums; ++v) S[v] = wl.rec[v][s];
+                        id = a.ids[start + p];
+                        planes_of(a, id, S, ox, oy, o);
+#pragma unroll
+                        for (int v = 0; v < kGradPlanes; ++v) wl.rec[v][s] = o[v];
                     }
-                    mask = vm;
-                    if (mask != 0) break;
+                    reinterpret_cast<uint32_t *>(wl.rec[9])[s] = id;
                 }
-                if (mask == 0) break;      // the list is done: the slots from s stay empty
-            }
-            {
-                const int b = 63 - __builtin_clzll(mask);
-                clear_bit(mask, b);
-                const Staged st = kRecompute ? read_staged_at(my_off + 48u * (uint32_t)b)
-                                             : read_staged_at(staged_off(my_off, b));
-                const uint32_t pos = lo + (uint32_t)b;
-                float u, w;
-                const float G = __builtin_amdgcn_exp2f(-exponent2(st, cx, cy, u, w));
-                const bool c = pos < nl && G > g_min;
-                const float araw = fmaf(st.q.w, G, -st.c.w);
-                const bool shaped = c && araw <= amax;       // alpha not clamped
-                const float acl = min_amax(araw, amax);
-                const float al = c ? acl : 0.f;
-                const float Tb = T * __builtin_amdgcn_rcpf(1.f - al);
-                const float wgt = al * Tb;
-                const float cg = fmaf(st.c.x, g0, fmaf(st.c.y, g1, st.c.z * g2));
-                const float e = cg - Ag;                     // (c - A) . g
-                const float abar = c ? Tb * e : 0.f;
-                Ag = fmaf(al, e, Ag);
-                T = Tb;
-                const float f = shaped ? abar : 0.f;
-                // f G and f straight into their moment registers (the
-                // positions past the table overwrite the first and
-                // ignore the tenth), so neither needs a copy
-                acc[kSums * s + 0] = f * G;
-                acc[kSums * s + 9] = f;
-                const float fG = acc[kSums * s + 0];
-                acc[kSums * s + 6] = wgt * g0;
-                acc[kSums * s + 7] = wgt * g1;
-                acc[kSums * s + 8] = wgt * g2;
-                if (pos < (uint32_t)tab_cap) {
-                    // moments about the tile centre (wave-uniform branch)
-                    const float fGx = fG * cx, fGy = fG * cy;
-                    acc[kSums * s + 1] = fGx;
-                    acc[kSums * s + 2] = fGy;
-                    acc[kSums * s + 3] = fGx * cx;
-                    acc[kSums * s + 4] = fGx * cy;
-                    acc[kSums * s + 5] = fGy * cy;
-                } else {
-                    // the planes without their constant factors (plane_scale);
-                    // the offset d = M^-1 (u, w)
-                    const float dx = (st.q.x * u - st.m.w * w) * st.q.z;
-                    const float dy = fmaf(st.q.y, u, st.m.z * w) * st.q.z;
-                    const float P = fG * st.q.w;             // -dL/dp
-                    const float Pdx = P * dx, Pdy = P * dy;
-                    acc[kSums * s + 0] = P * fmaf(u, st.m.z, -w * st.q.y);
-                    acc[kSums * s + 1] = P * fmaf(u, st.m.w, w * st.q.x);
-                    acc[kSums * s + 2] = Pdx * dx;
-                    acc[kSums * s + 3] = Pdx * dy;
-                    acc[kSums * s + 4] = Pdy * dy;
-                    acc[kSums * s + 5] = fmaf(-g_min, f, fG);    // f (G - g_min)
-                    // acc[kSums * s + 9] is not stored for these
-                    // positions: the reduction sums each index on its own
-                }
-                slot_pos[s] = pos;
-                filled = s + 1;
+                wave_lds_sync();
+                add_grads(a, &wl.rec[0][s0], 64, reinterpret_cast<uint32_t *>(&wl.rec[9][s0]),
+                          n - s0 < kGroup ? n - s0 : kGroup, lane);
             }
         }
-        if (filled == 0) break;
-        // the registers past kSums * kSlots feed only sums that are never
-        // stored: setting them here keeps them out of the registers live
-        // across the slot loop
-#pragma unroll
-        for (int i = kSums * kSlots; i < kAcc; ++i) acc[i] = 0.f;
-        const float r = reduce_scatter32(acc, lane);
-        uint32_t my_pos = slot_pos[0];
-#pragma unroll
-        for (int i = 1; i < kSlots; ++i) my_pos = my_s == i ? slot_pos[i] : my_pos;
-        if (my_store && my_s < filled) {
-            if (my_pos < (uint32_t)tab_cap)
-                atomicAdd(&table[my_v * tab_cap + my_pos], r);
-            else if (my_v < kGradPlanes)
-                atomicAdd(a.d_gauss + (int64_t)my_v * ng + a.ids[start + my_pos],
-                          r * plane_scale(my_v, inv_1mg));
-        }
+        wave_lds_sync();
+        const uint32_t rest = lane < qn - n ? wl.pos[64 + lane] : 0u;
+        wave_lds_sync();
+        if (lane < qn - n) wl.pos[lane] = rest;
+        qn -= n;
     }
     __syncthreads();
-    // the table's moments to the nine planes, one position per thread
-    for (int p = threadIdx.x; p < tab_n; p += blockDim.x) {
-        float S[kSums];
+    // the table's moments to the nine planes, 64 positions per wave at a time
+    uint32_t *fid = reinterpret_cast<uint32_t *>(wl.rec[9]);
+    for (int p0 = 64 * w; p0 < tab_n; p0 += 64 * nwaves) {
+        const int p = p0 + lane;
+        float S[kSums], o[kGradPlanes];
         bool any = false;
 #pragma unroll
         for (int v = 0; v < kSums; ++v) {
-            S[v] = table[v * tab_cap + p];
+            S[v] = p < tab_n ? (float)table[v * tab_p + p] : 0.f;
             any |= S[v] != 0.f;
         }
-        if (!any) continue;
-        const uint32_t id = a.ids[start + p];
-        const float4 m = a.rec[3 * (int64_t)id];
-        const float4 q = a.rec[3 * (int64_t)id + 1];
-        const float mx = (m.x - ox) + m.z, my = (m.y - oy) + m.w;   // mean - tile centre
-        const float ex = kHalfLog2eSqrt * q.x, ey = kHalfLog2eSqrt * q.y;
-        const float fx = q.z * ex, fy = q.z * ey;
-        const float op = q.w * inv_1mg;
-        // sums over the tile's pixels of f G (dx, dy, dx^2, dx dy, dy^2), d = pixel - mean
-        const float sx = fmaf(-mx, S[0], S[1]), sy = fmaf(-my, S[0], S[2]);
-        const float sxx = fmaf(-mx, S[1] + sx, S[3]);
-        const float sxy = fmaf(-mx, sy, fmaf(-my, S[1], S[4]));
-        const float syy = fmaf(-my, S[2] + sy, S[5]);
-        const float A = fmaf(ex, ex, fy * fy), B = fmaf(ex, ey, -fx * fy),
-                    C = fmaf(ey, ey, fx * fx);
-        const float k2 = 1.38629436112f * op;        // 2 ln 2 o'
-        float out[kGradPlanes];
-        out[0] = k2 * fmaf(A, sx, B * sy);
-        out[1] = k2 * fmaf(B, sx, C * sy);
-        out[2] = -0.5f * op * sxx;
-        out[3] = -op * sxy;
-        out[4] = -0.5f * op * syy;
-        out[5] = fmaf(-g_min, S[9], S[0]) * inv_1mg;
-        out[6] = S[6];
-        out[7] = S[7];
-        out[8] = S[8];
+        uint32_t id = kNoGauss;
+        if (any) {
+            id = a.ids[start + p];
+            planes_of(a, id, S, ox, oy, o);
 #pragma unroll
-        for (int v = 0; v < kGradPlanes; ++v)
-            if (out[v] != 0.f) atomicAdd(a.d_gauss + (int64_t)v * ng + id, out[v]);
+            for (int v = 0; v < kGradPlanes; ++v) wl.rec[v][lane] = o[v];
+        }
+        fid[lane] = id;
+        wave_lds_sync();
+        add_grads(a, &wl.rec[0][0], 64, fid, tab_n - p0 < 64 ? tab_n - p0 : 64, lane);
+        wave_lds_sync();
     }
 }
 
-// Held to 80 VGPRs (six waves per SIMD; it needs 77, without spills), which
-// matches the six blocks per CU its LDS allows: the pass waits on memory
-// (records, tile ids, atomics) for a large part of its time, so resident waves
-// count more than instruction count.
+// Bound by VALU issue: 565 M instructions on the 2048x2048 frame (11.1 M slots),
+// about 80% of the SIMD cycles.  1,480 us in the form of one lane per pixel with a
+// 64-lane reduction per slot, float LDS atomics and plane atomics; 1,075 us in
+// this one (2040x1344 with 2,048 closed curves: 867 -> 630; 128x128: 101 -> 55, where
+// one staging per 64 entries instead of per batch shortens the chain of loads).
+// Products on the matrix cores (v_mfma_f32_16x16x4_f32 for u, w, c . g and the
+// sums) measured no faster than the first form: FP32 products issue at the
+// vector rate there and do not overlap with vector instructions.
 template <bool kRecompute>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_bwd_tiles(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_tiles(
     TileArgs a) {
     if (a.status[1] & Status::kOverflow) return;         // whole grid
     for_tiles(a, [&](int tile) { bwd_tile<kRecompute>(a, tile); });
@@ -1010,9 +1180,13 @@ __global__ void k_zero(float *p, int64_t n) {
 // dynamic LDS is laid out for.
 // Eight waves per SIMD (at most 64 VGPRs; 49 used): the stage waits on
 // latency, and at seven it ran 5% slower.
-template <int NT>
+//
+// kPacked: d_gauss holds nine floats per Gaussian, and the nine planes are
+// written to planes as they are read.
+template <int NT, bool kPacked>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bwd_curves(bz_curves c, int lk, int lg, double inv_rho2,
                                                    double s0, const float *__restrict__ d_gauss,
+                                                   float *__restrict__ planes,
                                                    int64_t ng, float *__restrict__ d_ctrl,
                                                    float *__restrict__ d_width,
                                                    float *__restrict__ d_color,
@@ -1087,7 +1261,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     for (int idx = lane, r = r0, k = k0; idx < n; idx += NT) {
         float dg[kGradPlanes];
 #pragma unroll
-        for (int q = 0; q < kGradPlanes; ++q) dg[q] = d_gauss[q * ng + v.g0 + idx];
+        for (int q = 0; q < kGradPlanes; ++q)
+            dg[q] = d_gauss[kPacked ? kGradPlanes * (v.g0 + idx) + q : q * ng + v.g0 + idx];
+        if (kPacked) {
+#pragma unroll
+            for (int q = 0; q < kGradPlanes; ++q) planes[q * ng + v.g0 + idx] = dg[q];
+        }
         // stencil (Eq. sigma with nearest-neighbour ends, Eq. rotation).  Row
         // r's samples are (1 - tau_r) XA + tau_r XB, so its differences along
         // the row are the same blend of DA and DB, and across rows
@@ -1448,16 +1627,16 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
 
 // Sum-table positions of a backward block whose batch masks take vis_bytes of
 // LDS (0 for the stored blend state): kTableCap less those bytes, in whole
-// multiples of 16 positions, at least 128.
+// multiples of 16 positions, at least 64.
 int table_cap(size_t vis_bytes) {
-    const int64_t per16 = (int64_t)(sizeof(float) * kSums * 16);
+    const int64_t per16 = (int64_t)(sizeof(double) * kSums * 16);
     const int64_t cut = ((int64_t)vis_bytes + per16 - 1) / per16 * 16;
-    return kTableCap - cut < 128 ? 128 : (int)(kTableCap - cut);
+    return kTableCap - cut < 64 ? 64 : (int)(kTableCap - cut);
 }
 
 hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
                             const bz_opts &o, const float *d_image, const bz_pixstate *st,
-                            float *d_gauss, hipStream_t s) {
+                            float *d_gauss, bool packed, hipStream_t s) {
     int64_t nz = (int64_t)kGradPlanes * n_gauss;
     if (nz > 0) {
         int64_t blocks = cdiv(nz, 256);
@@ -1467,11 +1646,13 @@ hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
     TileArgs a = tile_args(rec, b, o);
     a.d_image = d_image;
     a.d_gauss = d_gauss;
+    a.packed = packed;
     a.n_gauss = n_gauss;
     int threads = o.tile_w * o.tile_h;
     const size_t vis = st ? 0 : sizeof(uint64_t) * kVisCap * (size_t)(threads / 64);
     a.tab_cap = table_cap(vis);
-    size_t lds = sizeof(Staged) * (size_t)threads + vis + sizeof(float) * kSums * (size_t)a.tab_cap;
+    size_t lds = sizeof(BwdWave) * (size_t)(threads / 64) + vis +
+                 sizeof(double) * kSums * (size_t)(a.tab_cap + kTabPad);
     if (st) {
         a.t_final = st->t_final;
         a.n_last = st->n_last;
@@ -1483,22 +1664,32 @@ hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,
-                             const bz_grads &gr, hipStream_t s) {
-    if (c.n_curves == 0) return hipSuccess;
+template <bool kPacked>
+void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, float *planes,
+                   const bz_grads &gr, hipStream_t s) {
     const double rho = (double)o.rho, inv_rho2 = 1.0 / (rho * rho), s0 = (double)o.sigma0_sq;
     if (c.max_gauss_per_curve > kSmallCurve) {
         const size_t lds = stage2_lds_bytes(c.max_k, c.max_gauss_per_curve);
-        hipLaunchKernelGGL(k_bwd_curves<kCurveThreads>, dim3(c.n_curves), dim3(kCurveThreads),
-                           lds, s, c, c.max_k, c.max_gauss_per_curve, inv_rho2, s0, d_gauss,
-                           c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
+        hipLaunchKernelGGL((k_bwd_curves<kCurveThreads, kPacked>), dim3(c.n_curves),
+                           dim3(kCurveThreads), lds, s, c, c.max_k, c.max_gauss_per_curve, inv_rho2,
+                           s0, d_gauss, planes, c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color,
+                           gr.d_opacity);
     }
     // a small curve has K <= its Gaussian count <= kSmallCurve
     const int lk = c.max_k < kSmallCurve ? c.max_k : kSmallCurve;
     const int lg = c.max_gauss_per_curve < kSmallCurve ? c.max_gauss_per_curve : kSmallCurve;
-    hipLaunchKernelGGL(k_bwd_curves<kWave>, dim3(c.n_curves), dim3(kWave), stage2_lds_bytes(lk, lg),
-                       s, c, lk, lg, inv_rho2, s0, d_gauss, c.n_gauss, gr.d_ctrl, gr.d_width,
-                       gr.d_color, gr.d_opacity);
+    hipLaunchKernelGGL((k_bwd_curves<kWave, kPacked>), dim3(c.n_curves), dim3(kWave),
+                       stage2_lds_bytes(lk, lg), s, c, lk, lg, inv_rho2, s0, d_gauss, planes,
+                       c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
+}
+
+hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,
+                             float *planes, const bz_grads &gr, hipStream_t s) {
+    if (c.n_curves == 0) return hipSuccess;
+    if (planes)
+        launch_curves<true>(c, o, d_gauss, planes, gr, s);
+    else
+        launch_curves<false>(c, o, d_gauss, nullptr, gr, s);
     return hipGetLastError();
 }
 

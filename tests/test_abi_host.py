@@ -360,3 +360,27 @@ def test_static_sample_bin_checks_arguments_and_size_on_host():
     assert need.value > bz.STATIC_SCRATCH_BYTES
     assert lib.bz_sample_bin_static(C.byref(_fake_curves()), C.byref(o), C.byref(g), C.byref(big),
                                     None) == bz.BZ_ERR_CAPACITY
+
+
+def test_scratch_backward_checks_its_arguments_on_host():
+    """bz_render_bwd_scratch: bz_render_bwd's refusals, and a missing, aliased
+    or small scratch, before any launch."""
+    lib = bz.load_library()
+    o = _opts()
+    cv, b = _fake_curves(), _fake_bins()
+    g = bz.Gaussians(16, 16, 4096)
+    gr = bz.Grads(4096, 4096, 4096, 4096, 4096)
+    need = C.c_int64(0)
+    assert lib.bz_bwd_scratch_size(16, C.byref(need)) == bz.BZ_OK and need.value == 16 * 36
+    assert lib.bz_bwd_scratch_size(-1, C.byref(need)) == bz.BZ_ERR_ARG
+    assert lib.bz_bwd_scratch_size(1, None) == bz.BZ_ERR_ARG
+
+    def call(dimg=8192, scratch=65536, nbytes=16 * 36, grads=gr):
+        return lib.bz_render_bwd_scratch(C.byref(cv), C.byref(g), C.byref(b), C.byref(o), dimg,
+                                         None, C.byref(grads), scratch, nbytes, None)
+    assert call(scratch=None) == bz.BZ_ERR_ARG
+    assert call(scratch=4096) == bz.BZ_ERR_ARG                 # d_gauss itself
+    assert call(nbytes=16 * 36 - 1) == bz.BZ_ERR_CAPACITY
+    assert call(dimg=None) == bz.BZ_ERR_ARG
+    assert call(grads=bz.Grads(None, 4096, 4096, 4096, 4096)) == bz.BZ_ERR_ARG
+    assert call(grads=bz.Grads(4096, 4096, 4096, 4096, None)) == bz.BZ_ERR_ARG
