@@ -53,6 +53,13 @@ __device__ inline uint16_t f_to_bf(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// two of them, nearest even, by the instruction that converts a pair
+__device__ inline uint32_t pack_bf16(float a, float b) {
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
 struct Shape {
     int n, h, w, c, k, r, s, p, ho, wo;
 };
@@ -431,6 +438,567 @@ __global__ __launch_bounds__(256) void k_igemm(GemmArgs args) {
             }
 }
 
+// ---------------------------------------------------------------------------
+// Forward and input gradient, vector form
+// ---------------------------------------------------------------------------
+//
+// For channel counts that are multiples of 8 and outputs that are multiples of
+// 4 (every layer of the proposal network).  Same sums in the same order as
+// k_igemm (k ascending in steps of 32 through the same instruction), but the
+// filters are operand A and the pixels operand B, so that
+//  - a lane's 8 consecutive k of a pixel are one 16-byte load of BF16 (two of
+//    FP32) straight from global memory into the operand, without index divisions
+//    or barriers: where a k slice lies relative to a pixel is a table entry per 8
+//    k;
+//  - a block lays its columns' filters out in LDS once, lane by lane as the
+//    instruction takes them, and each of its waves then goes through row tiles of
+//    16 pixels on its own, the next k steps' pixels in flight in a second set of
+//    registers.
+// Bound by HBM: the first layer writes 134 MB of BF16 at 1024 images, the second
+// layer's input gradient moves 470 MB (FP32 gradients and the mask).  Before (k_igemm
+// on every shape) -> now, at 1024 images of 32 x 32: first layer 83 -> 52 us (2.9
+// TB/s), second 62 -> 45, its input gradient 292 -> 148 us (3.2 TB/s); at 256: 26
+// -> 20, 22 -> 17, 78 -> 37 us, the 1 x 1 head 18 -> 12.  k steps in flight: 4
+// (forward) and 2 (the FP32 side); half as many cost the second layer's input
+// gradient 14%, twice as many the last layers' 15%.
+struct ConvTab {
+    int off;              // elements from the pixel's base to the slice
+    int16_t dy, dx;       // rows and columns from it (bounds test)
+};
+
+// A parity class (forward: the only one): its steps of 32 k and where they start.
+struct ConvClass {
+    int first, steps, cy, cx;
+};
+
+// The slice at class k `k` of g's current class, relative to the pixel's base.
+template <int MODE>
+__device__ inline ConvTab conv_tab(const GemmArgs &g, int k) {
+    const Shape &S = g.S;
+    ConvTab e;
+    const int sc = MODE == kFwd ? S.c : S.k;
+    const int j = k / sc, ch = k - j * sc;
+    if (MODE == kFwd) {
+        const int ky = j / S.r, kx = j - ky * S.r;
+        e.dy = (int16_t)ky;
+        e.dx = (int16_t)kx;
+        e.off = (ky * S.w + kx) * S.c + ch;
+    } else {
+        const int y = j / g.nkx, x = j - y * g.nkx;
+        const int dy = (g.cy + S.p - g.ky0) / S.s - y, dx = (g.cx + S.p - g.kx0) / S.s - x;
+        e.dy = (int16_t)dy;
+        e.dx = (int16_t)dx;
+        e.off = (dy * S.wo + dx) * S.k + ch;
+    }
+    if (k >= g.K) e.dy = 0x4000;                // no such slice: out of every bound
+    return e;
+}
+
+// Wave-level LDS ordering.
+__device__ inline void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS of a block: the filters of its columns, lane by lane; the slice table; the
+// classes; an output tile of 16 pixels per wave.
+__host__ __device__ inline int conv_steps(int K) { return (K + 31) / 32; }
+__host__ __device__ inline int conv_pitch(int nb, int out_bytes) { return 16 * nb * out_bytes + 16; }
+inline size_t conv_rows_lds(int64_t steps, int classes, int nb, int out_bytes, int waves) {
+    return (size_t)steps * (nb * 1024 + 4 * sizeof(ConvTab)) + classes * sizeof(ConvClass) +
+           (size_t)waves * 16 * conv_pitch(nb, out_bytes);
+}
+
+// Division of 0 <= m < 2^31 by d >= 1 without a divide per tile (Granlund and
+// Montgomery 1994): with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d) < 2^32,
+// m / d = (m * mul) >> (31 + s).
+struct Divisor {
+    uint32_t d, mul;
+    int sh;
+};
+
+__device__ inline Divisor divisor(int d) {
+    const int s = d > 1 ? 32 - __builtin_clz(d - 1) : 1;
+    return Divisor{(uint32_t)d, (uint32_t)(((1ull << (31 + s)) + d - 1) / (unsigned)d), s - 1};
+}
+
+__device__ inline int divide(int m, const Divisor &v) {
+    return v.d == 1 ? m : (int)(__umulhi((uint32_t)m, v.mul) >> v.sh);
+}
+
+// One row tile as a wave reads it: this lane's output pixel, or its block of
+// stride x stride input pixels, one of each class (input gradient).
+struct ConvRow {
+    int base, y0, x0, b;
+};
+
+template <int MODE>
+__device__ inline ConvRow conv_row(const GemmArgs &g, const Divisor &image, const Divisor &line,
+                                   int tile, int j) {
+    const Shape &S = g.S;
+    ConvRow r;
+    const int m = tile * 16 + j;
+    r.b = divide(m, image);
+    const int rem = m - r.b * (int)image.d;
+    const int ry = divide(rem, line), rx = rem - ry * (int)line.d;
+    r.y0 = MODE == kFwd ? ry * S.s - S.p : ry;
+    r.x0 = MODE == kFwd ? rx * S.s - S.p : rx;
+    r.base = MODE == kFwd ? ((r.b * S.h + r.y0) * S.w + r.x0) * S.c
+                          : ((r.b * S.ho + ry) * S.wo + rx) * S.k;
+    if (r.b >= S.n) r.y0 = -0x4000;             // no such row: out of every bound
+    return r;
+}
+
+// The pixel that the lane's sums belong to, or -1.
+template <int MODE>
+__device__ inline int conv_out(const GemmArgs &g, const ConvRow &r, int tile, int j,
+                               const ConvClass &cls) {
+    const Shape &S = g.S;
+    if (r.b >= S.n) return -1;
+    if (MODE == kFwd) return tile * 16 + j;
+    const int iy = r.y0 * S.s + cls.cy, ix = r.x0 * S.s + cls.cx;
+    return iy < S.h && ix < S.w ? (r.b * S.h + iy) * S.w + ix : -1;
+}
+
+template <int MODE, int NB>
+__global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_steps,
+                                                    int classes) {
+    constexpr int KS = MODE == kFwd ? 4 : 2;       // steps of 32 k in flight at a time
+    constexpr int kV = MODE == kFwd ? 1 : 2;    // 16-byte loads per slice
+    constexpr int kOutB = MODE == kFwd ? 2 : 4; // bytes per output
+    constexpr int kPer = 16 / kOutB;            // channels per 16 bytes
+    extern __shared__ __align__(16) unsigned char s_conv[];
+    GemmArgs g = args;
+    const Shape &S = g.S;
+    const int t = threadIdx.x, nt = blockDim.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int j = lane & 15, q = lane >> 4;
+    const int n0 = (int)blockIdx.y * 16 * NB;
+    const int kf = S.r * S.r * S.c;
+    // sW[step][nb][lane][8 k]
+    uint16_t *sW = reinterpret_cast<uint16_t *>(s_conv);
+    ConvTab *s_tab = reinterpret_cast<ConvTab *>(s_conv + (size_t)most_steps * NB * 1024);
+    ConvClass *s_cls = reinterpret_cast<ConvClass *>(s_tab + 4 * most_steps);
+    unsigned char *out = reinterpret_cast<unsigned char *>(s_cls + classes) +
+                         wave * 16 * conv_pitch(NB, kOutB);
+    for (int z = 0, first = 0; z < classes; ++z) {
+        if (MODE == kBwdData) set_class(g, (int)blockIdx.z * classes + z);
+        const int steps = conv_steps(g.K);
+        if (t == 0) s_cls[z] = ConvClass{first, steps, g.cy, g.cx};
+        for (int i = t; i < 4 * steps; i += nt) s_tab[4 * first + i] = conv_tab<MODE>(g, 8 * i);
+        uint16_t *const dst = sW + first * NB * 512;
+        if (MODE == kFwd) {
+            // 8 k of one output channel per load, one lane's slice
+            for (int u = t; u < steps * NB * 64; u += nt) {
+                const int ln = u & 63, nb = (u >> 6) % NB, st = u / (64 * NB);
+                const int n = n0 + 16 * nb + (ln & 15), k = 32 * st + 8 * (ln >> 4);
+                uint4 w = make_uint4(0, 0, 0, 0);
+                if (n < g.N && k < g.K) w = *reinterpret_cast<const uint4 *>(g.w + (n * kf + k));
+                *reinterpret_cast<uint4 *>(dst + 8 * u) = w;
+            }
+        } else {
+            // one k of 8 input channels per load, a column of 8 lanes' slices
+            for (int u = t; u < steps * 32 * 2 * NB; u += nt) {
+                const int n8 = u % (2 * NB), k = u / (2 * NB), n = n0 + 8 * n8;
+                uint4 w = make_uint4(0, 0, 0, 0);
+                if (n < g.N && k < g.K) {
+                    const int jt = k / S.k, co = k - jt * S.k;
+                    w = *reinterpret_cast<const uint4 *>(g.w +
+                                                         (co * kf + cls_tap(g, jt) * S.c + n));
+                }
+                const int ln = ((k >> 3) & 3) * 16 + (n8 & 1) * 8;
+                uint16_t *d = dst + 8 * (((k >> 5) * NB + (n8 >> 1)) * 64 + ln) + (k & 7);
+                const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) d[8 * e] = (uint16_t)(w4[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+        first += steps;
+    }
+    __syncthreads();                            // the block's only barrier
+    const Divisor image = divisor(MODE == kFwd ? S.ho * S.wo
+                                               : ((S.h + S.s - 1) / S.s) * ((S.w + S.s - 1) / S.s));
+    const Divisor line = divisor(MODE == kFwd ? S.wo : (S.w + S.s - 1) / S.s);
+    const int tiles = (int)(((int64_t)S.n * image.d + 15) / 16);
+    const int SH = MODE == kFwd ? S.h : S.ho, SW = MODE == kFwd ? S.w : S.wo;
+    const int nwaves = (nt >> 6) * (int)gridDim.x;
+    // workgroup b runs on XCD b % 8: neighbouring row tiles, which share input
+    // pixels, go to the same one
+    const int gx = (int)gridDim.x, bx = (int)blockIdx.x;
+    const int vb = gx % 8 ? bx : (bx % 8) * (gx / 8) + bx / 8;
+    int tile = vb * (nt >> 6) + wave;
+    int z = 0, c = 0;                           // the class and the chunk being multiplied
+    if (tile >= tiles || n0 >= g.N) return;
+    floatx4 acc[NB];
+    floatx4 bias[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        acc[nb] = bias[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const int n = n0 + 16 * nb + 4 * q;
+        if (MODE == kFwd && g.bias && n < g.N) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bias[nb][e] = g.bias[n + e];
+        }
+    }
+    const int nc = g.N - n0 < 16 * NB ? g.N - n0 : 16 * NB;   // channels of this block
+    const int per_px = nc / kPer;               // 16-byte pieces of a pixel
+    const int px0 = lane / per_px, ch0 = lane - px0 * per_px;
+    const bool via_lds = MODE == kBwdData || (g.out_b && g.N % kPer == 0);
+
+    auto load = [&](const ConvRow &r, const ConvClass &cls, int ch, uint4 (&px)[KS][kV]) {
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+#pragma unroll
+            for (int v = 0; v < kV; ++v) px[st][v] = make_uint4(0, 0, 0, 0);
+            if (ch * KS + st >= cls.steps) continue;        // uniform
+            const ConvTab e = s_tab[4 * (cls.first + ch * KS + st) + q];
+            if ((unsigned)(r.y0 + e.dy) < (unsigned)SH && (unsigned)(r.x0 + e.dx) < (unsigned)SW) {
+                const uint4 *p =
+                    MODE == kFwd ? reinterpret_cast<const uint4 *>(g.x + (r.base + e.off))
+                                 : reinterpret_cast<const uint4 *>(g.dy + (r.base + e.off));
+#pragma unroll
+                for (int v = 0; v < kV; ++v) px[st][v] = p[v];
+            }
+        }
+    };
+    auto multiply = [&](const ConvClass &cls, int ch, const uint4 (&px)[KS][kV]) {
+#pragma unroll
+        for (int st = 0; st < KS; ++st) {
+            if (ch * KS + st >= cls.steps) continue;        // uniform
+            bf16x8 p;
+            if (MODE == kFwd) {
+                p = __builtin_bit_cast(bf16x8, px[st][0]);
+            } else {
+                const floatx4 lo = __builtin_bit_cast(floatx4, px[st][0]);
+                const floatx4 hi = __builtin_bit_cast(floatx4, px[st][kV - 1]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    p[e] = (__bf16)lo[e];                   // nearest even
+                    p[e + 4] = (__bf16)hi[e];
+                }
+            }
+            const uint16_t *w = sW + 8 * ((cls.first + ch * KS + st) * NB * 64 + lane);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    *reinterpret_cast<const bf16x8 *>(w + 8 * 64 * nb), p, acc[nb], 0, 0, 0);
+        }
+    };
+    constexpr int kPieces = (4 * NB * kOutB + 15) / 16;     // of 16 bytes per lane
+    // A lane holds channels 4 q .. 4 q + 3 of each 16 for pixel j.  Stored from
+    // there, an instruction would write 32 or 64 bytes of each of 16 pixels;
+    // through LDS consecutive lanes write consecutive 16 bytes.
+    auto store = [&](int opix) {
+        constexpr int kPitch = 16 * NB * kOutB + 16;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = n0 + 16 * nb + 4 * q;
+            floatx4 v = acc[nb];
+            acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (n >= g.N) continue;
+            const int at = opix * g.N + n;
+            if (MODE == kFwd) {
+                if (g.bias) v += bias[nb];
+                if (g.relu) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+                }
+                if (g.out_f && opix >= 0) *reinterpret_cast<floatx4 *>(g.out_f + at) = v;
+                if (g.out_b) {
+                    const uint2 h = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                    if (via_lds)
+                        *reinterpret_cast<uint2 *>(out + j * kPitch + (n - n0) * kOutB) = h;
+                    else if (opix >= 0)
+                        *reinterpret_cast<uint2 *>(g.out_b + at) = h;
+                }
+            } else {
+                *reinterpret_cast<floatx4 *>(out + j * kPitch + (n - n0) * kOutB) = v;
+            }
+        }
+        if (!via_lds) return;
+        wave_fence();
+        int px = px0, piece = ch0;
+#pragma unroll
+        for (int it = 0; it < kPieces; ++it) {
+            const int po = __shfl(opix, px & 15);
+            uint4 d = *reinterpret_cast<const uint4 *>(out + (px & 15) * kPitch + 16 * piece);
+            const bool ok = px < 16 && po >= 0;
+            const int o = po * g.N + n0 + piece * kPer;
+            px += 64 / per_px;
+            piece += 64 % per_px;
+            if (piece >= per_px) {
+                piece -= per_px;
+                ++px;
+            }
+            if (!ok) continue;
+            if (MODE == kFwd) {
+                *reinterpret_cast<uint4 *>(g.out_b + o) = d;
+            } else {
+                if (g.mask) {
+                    const uint2 h = *reinterpret_cast<const uint2 *>(g.mask + o);
+                    if (!(bf_to_f((uint16_t)h.x) > 0.f)) d.x = 0u;
+                    if (!(bf_to_f((uint16_t)(h.x >> 16)) > 0.f)) d.y = 0u;
+                    if (!(bf_to_f((uint16_t)h.y) > 0.f)) d.z = 0u;
+                    if (!(bf_to_f((uint16_t)(h.y >> 16)) > 0.f)) d.w = 0u;
+                }
+                *reinterpret_cast<uint4 *>(g.out_f + o) = d;
+            }
+        }
+        wave_fence();
+    };
+    // Two sets of registers in turn: one chunk's pixels travel while the other's
+    // are multiplied, across the ends of classes and tiles too.
+    auto class_of = [&](int i) {
+        const ConvClass v = s_cls[i];
+        return ConvClass{__builtin_amdgcn_readfirstlane(v.first),
+                         __builtin_amdgcn_readfirstlane(v.steps),
+                         __builtin_amdgcn_readfirstlane(v.cy), __builtin_amdgcn_readfirstlane(v.cx)};
+    };
+    ConvRow row = conv_row<MODE>(g, image, line, tile, j);
+    ConvClass cls = class_of(0);
+    uint4 pa[KS][kV], pb[KS][kV];
+    load(row, cls, 0, pa);
+    auto advance = [&](const uint4 (&cur)[KS][kV], uint4 (&nxt)[KS][kV]) {
+        const bool done = (c + 1) * KS >= cls.steps;        // the class's last chunk
+        const int opix = conv_out<MODE>(g, row, tile, j, cls);
+        const ConvClass ccls = cls;
+        const int cc = c;
+        if (!done) {
+            ++c;
+        } else {
+            c = 0;
+            if (++z == classes) {
+                z = 0;
+                tile += nwaves;
+                if (tile < tiles) row = conv_row<MODE>(g, image, line, tile, j);
+            }
+            if (MODE == kBwdData) cls = class_of(z);
+        }
+        if (tile < tiles) load(row, cls, c, nxt);
+        multiply(ccls, cc, cur);
+        if (done) store(opix);
+        return tile < tiles;
+    };
+    while (advance(pa, pb) && advance(pb, pa)) {}
+}
+
+inline bool aligned(const void *p, uintptr_t n) { return ((uintptr_t)p & (n - 1)) == 0; }
+
+// Does the vector form serve the call?  Its loads and stores are 16 and 8 bytes
+// wide: channel counts and pointers decide.
+template <int MODE>
+bool conv_rows_serves(const GemmArgs &g) {
+    const Shape &S = g.S;
+    if (S.c % 8 || g.N % 4 || (MODE == kBwdData && S.k % 8)) return false;
+    // 16-bit rows and columns of the slice table; blockIdx.y
+    const int most = 0x2000;
+    if (S.h >= most || S.w >= most || g.N >= (1 << 19)) return false;
+    return aligned(MODE == kFwd ? (const void *)g.x : (const void *)g.dy, 16) && aligned(g.w, 16) &&
+           aligned(g.out_f, 16) && aligned(g.out_b, 16) && aligned(g.mask, 8);
+}
+
+template <int MODE, int NB>
+void launch_conv_rows(const GemmArgs &g, int64_t rows, int steps, int classes, int groups,
+                      hipStream_t s) {
+    constexpr int kOutB = MODE == kFwd ? 2 : 4;
+    const int64_t tiles = cdiv(rows, 16), cols = cdiv(g.N, 16 * NB);
+    // the filters' LDS decides how many blocks a CU holds: 16 waves in one block
+    // where two blocks do not fit
+    const int waves = conv_rows_lds(steps, classes, NB, kOutB, 8) > 80 * 1024 ? 16 : 8;
+    const size_t lds = conv_rows_lds(steps, classes, NB, kOutB, waves);
+    // resident blocks only: a wave takes several tiles, its filters loaded once
+    const int64_t per_cu = lds > 80 * 1024 || waves == 16 ? 1 : lds > 53 * 1024 ? 2 : 3;
+    int64_t gx = cdiv(tiles, waves);
+    const int64_t most = cdiv(256 * per_cu, cols * groups);
+    if (gx > most) gx = most;
+    hipLaunchKernelGGL((k_conv_rows<MODE, NB>), dim3((unsigned)gx, (unsigned)cols, (unsigned)groups),
+                       dim3(64 * waves), lds, s, g, steps, classes);
+}
+
+// rows: output pixels, or blocks of stride x stride input pixels.  Steps of 32 k:
+// over all classes, and in the class with most.  False: the filters of 16 output
+// channels do not fit.
+//
+// A block takes 64 output channels and, for the input gradient, all classes of its
+// pixel blocks (their output gradients are then read once, and no class's waves
+// end early: 163 -> 147 us for the second layer at 1024 images against a class per
+// block).  Where that would leave CUs without a block it takes one class, and
+// below that 16 channels
+// (all classes together there: the third layer at 256 images 14 -> 23 us).
+template <int MODE>
+bool try_conv_rows(const GemmArgs &g, int64_t rows, int64_t steps, int64_t longest, int classes,
+                   hipStream_t s) {
+    constexpr int kOutB = MODE == kFwd ? 2 : 4;
+    constexpr size_t kMost = 144 * 1024;
+    if (!conv_rows_serves<MODE>(g) || longest > 4096) return false;
+    const int64_t wide = cdiv(rows, 16 * 8) * cdiv(g.N, 64);
+    if (wide >= 192 && conv_rows_lds(steps, classes, 4, kOutB, 16) <= kMost)
+        launch_conv_rows<MODE, 4>(g, rows, (int)steps, classes, 1, s);
+    else if (wide * classes >= 192 && conv_rows_lds(longest, 1, 4, kOutB, 16) <= kMost)
+        launch_conv_rows<MODE, 4>(g, rows, (int)longest, 1, classes, s);
+    else if (conv_rows_lds(longest, 1, 1, kOutB, 16) <= kMost)
+        launch_conv_rows<MODE, 1>(g, rows, (int)longest, 1, classes, s);
+    else
+        return false;
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// Filter and bias gradient, vector form
+// ---------------------------------------------------------------------------
+//
+// For channel counts that are multiples of 8.  A workgroup takes 64 output
+// channels by 64 (tap, input channel) columns over k_chunk output pixels, 128
+// at a time: a thread loads 8 channels of 4 consecutive pixels of each operand
+// (16 bytes per load) and writes them to LDS with the pixels contiguous, as the
+// matrix instruction takes them, 8 bytes per channel; the next 128 pixels'
+// loads are in flight meanwhile.  The first column block also sums the output
+// gradients (FP32) into the bias gradient.  Bound by the operands' way from
+// the L2 (each of the 9 column tiles of a 64-channel 3 x 3 layer reads both), so
+// the tiles of a chunk share an XCD: second layer at 1024 images 137 -> 100 us.
+// Before (k_igemm and a bias pass) -> now: that layer 176 -> 89 us, at 256 images
+// 60 -> 35, the three after it 29 -> 15, 18 -> 11 and 16 -> 11 us.
+// Workgroups of the filter gradient: more of them mean more float atomics on dw
+// (64-byte requests to memory at about 20 G/s), fewer a longer tail.  The third
+// layer at 256 images takes 15 us with 512 and 17 with 1024; the second at 1024
+// images 100 and 89 (and 140 with 256).
+constexpr int kWgGroups = 512;
+constexpr int kWgPix = 128;
+constexpr int kWgPitch = kWgPix + 4;        // 66 words: eight rows apart, other banks
+
+__global__ __launch_bounds__(256) void k_wgrad(GemmArgs g, float *db) {
+    __shared__ __align__(16) uint16_t sA[64][kWgPitch], sB[64][kWgPitch];
+    __shared__ float s_db[8][64];
+    const Shape &S = g.S;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int cg = t & 7, pg = t >> 3;          // 8 channels, 4 pixels
+    // workgroup b runs on XCD b % 8: the tiles of a chunk of pixels, which read the
+    // same operands, on one XCD
+    const int tm = (g.M + 63) / 64, tn = (g.N + 63) / 64, tiles = tm * tn;
+    const int b8 = (int)blockIdx.x / (8 * tiles), in8 = (int)blockIdx.x - b8 * 8 * tiles;
+    const int tile = in8 / 8, m0 = (tile % tm) * 64, n0 = (tile / tm) * 64;
+    const int chunk = b8 * 8 + in8 % 8, chunks = (g.K + g.k_chunk - 1) / g.k_chunk;
+    if (chunk >= chunks) return;
+    const int kbeg = chunk * g.k_chunk;
+    const int kend = kbeg + g.k_chunk < g.K ? kbeg + g.k_chunk : g.K;
+    const int co = m0 + 8 * cg, n = n0 + 8 * cg;
+    const int tap = n / S.c, ci = n - tap * S.c, ky = tap / S.r, kx = tap - ky * S.r;
+    const bool ok_a = co < g.M, ok_b = n < g.N;
+    const bool sum_db = db && n0 == 0;
+    floatx4 a[4][2];
+    uint4 b[4];
+    float bs[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bs[e] = 0.f;
+    auto fetch = [&](int k0) {
+        const int k = k0 + 4 * pg;
+        const int hw = S.ho * S.wo;
+        int img = k / hw;
+        const int rem = k - img * hw;
+        int oy = rem / S.wo, ox = rem - oy * S.wo;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i][0] = a[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            b[i] = make_uint4(0, 0, 0, 0);
+            if (k + i < kend) {
+                if (ok_a) {
+                    const floatx4 *p = reinterpret_cast<const floatx4 *>(g.dy + ((k + i) * S.k + co));
+                    a[i][0] = p[0];
+                    a[i][1] = p[1];
+                }
+                const int iy = oy * S.s - S.p + ky, ix = ox * S.s - S.p + kx;
+                if (ok_b && (unsigned)iy < (unsigned)S.h && (unsigned)ix < (unsigned)S.w)
+                    b[i] = *reinterpret_cast<const uint4 *>(
+                        g.x + (((img * S.h + iy) * S.w + ix) * S.c + ci));
+            }
+            if (++ox == S.wo) {
+                ox = 0;
+                if (++oy == S.ho) {
+                    oy = 0;
+                    ++img;
+                }
+            }
+        }
+    };
+    const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, q = lane >> 4;
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int jn = 0; jn < 2; ++jn) acc[i][jn] = floatx4{0.f, 0.f, 0.f, 0.f};
+    fetch(kbeg);
+    for (int k0 = kbeg; k0 < kend; k0 += kWgPix) {
+        __syncthreads();                        // the previous pixels are read
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v0 = a[0][e >> 2][e & 3], v1 = a[1][e >> 2][e & 3];
+            const float v2 = a[2][e >> 2][e & 3], v3 = a[3][e >> 2][e & 3];
+            if (sum_db) bs[e] += (v0 + v1) + (v2 + v3);
+            *reinterpret_cast<uint2 *>(&sA[8 * cg + e][4 * pg]) =
+                make_uint2(pack_bf16(v0, v1), pack_bf16(v2, v3));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint32_t w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t w4[4] = {b[i].x, b[i].y, b[i].z, b[i].w};
+                w[i] = w4[e >> 1];
+            }
+            // the low or high halves of two pixels side by side
+            const uint32_t sel = e & 1 ? 0x07060302u : 0x05040100u;
+            *reinterpret_cast<uint2 *>(&sB[8 * cg + e][4 * pg]) =
+                make_uint2(__builtin_amdgcn_perm(w[1], w[0], sel),
+                           __builtin_amdgcn_perm(w[3], w[2], sel));
+        }
+        __syncthreads();
+        if (k0 + kWgPix < kend) fetch(k0 + kWgPix);
+#pragma unroll
+        for (int ks = 0; ks < kWgPix / 32; ++ks) {
+            bf16x8 fa[2], fb[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint2 *pa =
+                    reinterpret_cast<const uint2 *>(&sA[wm * 32 + i * 16 + r16][ks * 32 + 8 * q]);
+                const uint2 *pb =
+                    reinterpret_cast<const uint2 *>(&sB[wn * 32 + i * 16 + r16][ks * 32 + 8 * q]);
+                const uint2 a0 = pa[0], a1 = pa[1], b0 = pb[0], b1 = pb[1];
+                fa[i] = __builtin_bit_cast(bf16x8, make_uint4(a0.x, a0.y, a1.x, a1.y));
+                fb[i] = __builtin_bit_cast(bf16x8, make_uint4(b0.x, b0.y, b1.x, b1.y));
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int jn = 0; jn < 2; ++jn)
+                    acc[i][jn] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[jn], acc[i][jn], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int jn = 0; jn < 2; ++jn)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int m = m0 + wm * 32 + i * 16 + 4 * q + e;
+                const int nn = n0 + wn * 32 + jn * 16 + r16;
+                if (m < g.M && nn < g.N) atomicAdd(&g.out_f[m * g.N + nn], acc[i][jn][e]);
+            }
+    if (!sum_db) return;                        // uniform over the block
+    // the 32 pixel groups' sums of a channel: 8 lanes apart in a wave, then the waves
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        bs[e] += __shfl_xor(bs[e], 8);
+        bs[e] += __shfl_xor(bs[e], 16);
+        bs[e] += __shfl_xor(bs[e], 32);
+        if (lane < 8) s_db[wave][8 * cg + e] = bs[e];
+    }
+    __syncthreads();
+    if (t < 64 && m0 + t < g.M)
+        atomicAdd(&db[m0 + t], (s_db[0][t] + s_db[1][t]) + (s_db[2][t] + s_db[3][t]));
+}
+
 // Dispatch on which operands can move 8 at a time.
 template <int MODE>
 void launch_igemm(const GemmArgs &g, bool va, bool vb, dim3 grid, hipStream_t s) {
@@ -444,9 +1012,12 @@ void launch_igemm(const GemmArgs &g, bool va, bool vb, dim3 grid, hipStream_t s)
         hipLaunchKernelGGL((k_igemm<MODE, false, false>), grid, dim3(256), 0, s, g);
 }
 
-__global__ void k_fill0(float *p, int64_t n) {
+// Filter and bias gradients cleared, in one launch (db may be null).
+__global__ void k_fill0(float *p, int64_t n, float *db, int k) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    if (db)
+        for (int64_t o = i; o < k; o += stride) db[o] = 0.f;
     for (; i < n; i += stride) p[i] = 0.f;
 }
 
@@ -740,6 +1311,7 @@ hipError_t launch_conv_fwd(const bz_conv &c, const uint16_t *x, const uint16_t *
     g.relu = relu;
     g.out_f = y;
     g.out_b = yb;
+    if (try_conv_rows<kFwd>(g, g.M, cdiv(g.K, 32), cdiv(g.K, 32), 1, s)) return hipGetLastError();
     dim3 grid((unsigned)cdiv(g.M, kBM), (unsigned)cdiv(g.N, kBN), 1);
     // A: 8 input channels per load (c % 8); B: 8 filter taps-channels per load (K % 8)
     launch_igemm<kFwd>(g, c.c % 8 == 0, g.K % 8 == 0 && c.c % 8 == 0, grid, s);
@@ -761,6 +1333,14 @@ hipError_t launch_conv_bwd_data(const bz_conv &c, const float *dy, const uint16_
     g.out_f = dx;
     const int st = c.stride;
     const int64_t rows = (int64_t)c.n * ((c.h + st - 1) / st) * ((c.w + st - 1) / st);  // class 0
+    int64_t steps = 0, longest = 0;             // of 32 k
+    for (int ky = 0; ky < st && ky < c.r; ++ky)
+        for (int kx = 0; kx < st && kx < c.r; ++kx) {
+            const int64_t n = cdiv((int64_t)cdiv(c.r - ky, st) * cdiv(c.r - kx, st) * c.k, 32);
+            steps += n;
+            longest = longest < n ? n : longest;
+        }
+    if (try_conv_rows<kBwdData>(g, rows, steps, longest, st * st, s)) return hipGetLastError();
     dim3 grid((unsigned)cdiv(rows, kBM), (unsigned)cdiv(g.N, kBN), (unsigned)(st * st));
     // A: 8 output channels of dy (k % 8); B: 8 input channels of a filter row (c % 8)
     launch_igemm<kBwdData>(g, c.k % 8 == 0, c.c % 8 == 0, grid, s);
@@ -778,24 +1358,29 @@ hipError_t launch_conv_bwd_weight(const bz_conv &c, const float *dy, const uint1
     g.x = x;
     g.out_f = dw;
     const int64_t tiles = cdiv(g.M, kBM) * cdiv(g.N, kBN);
-    g.k_chunk = cdiv(g.K, kSplitRows) * tiles < kSplitMinGroups ? kSplitRowsSmall : kSplitRows;
-    const int64_t nz = g.M * g.N;
+    const int64_t nz = (int64_t)g.M * g.N;
     hipLaunchKernelGGL(k_fill0, dim3((unsigned)cdiv(nz, 256) < 4096 ? (unsigned)cdiv(nz, 256) : 4096),
-                       dim3(256), 0, s, dw, nz);
+                       dim3(256), 0, s, dw, nz, db, c.k);
     if (wgrad_first_shape(c) && ((uintptr_t)x & 15) == 0) {     // 16-byte image loads
-        if (db)
-            hipLaunchKernelGGL(k_fill0, dim3(1), dim3(256), 0, s, db, (int64_t)c.k);
         if (c.c == 1) launch_wgrad_first<1>(c, dy, x, dw, db, s);
         else if (c.c == 2) launch_wgrad_first<2>(c, dy, x, dw, db, s);
         else launch_wgrad_first<3>(c, dy, x, dw, db, s);
         return hipGetLastError();
     }
+    if (c.k % 8 == 0 && c.c % 8 == 0 && aligned(dy, 16) && aligned(x, 16)) {
+        // about kWgGroups workgroups, twice as many over 1024 pixels for each
+        int64_t splits = cdiv(kWgGroups, tiles);
+        if (g.K > 1024 * splits) splits *= 2;
+        g.k_chunk = (int)(cdiv(cdiv(g.K, splits), kWgPix) * kWgPix);
+        const int64_t chunks8 = cdiv(cdiv(g.K, g.k_chunk), 8) * 8;
+        hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(tiles * chunks8)), dim3(256), 0, s, g, db);
+        return hipGetLastError();
+    }
+    g.k_chunk = cdiv(g.K, kSplitRows) * tiles < kSplitMinGroups ? kSplitRowsSmall : kSplitRows;
     dim3 grid((unsigned)cdiv(g.M, kBM), (unsigned)cdiv(g.N, kBN), (unsigned)cdiv(g.K, g.k_chunk));
     // A: 8 output channels of dy (k % 8); B: 8 input channels of a shifted pixel (c % 8)
     launch_igemm<kBwdWeight>(g, c.k % 8 == 0, c.c % 8 == 0, grid, s);
     if (db) {
-        hipLaunchKernelGGL(k_fill0, dim3((unsigned)cdiv(c.k, 256)), dim3(256), 0, s, db,
-                           (int64_t)c.k);
         // dy rows are 16-byte aligned when k % 4 == 0 (dy itself is)
         const int64_t chunk = bias_chunk(g.K);
         if (c.k % 4 == 0 && c.k <= 64 && ((uintptr_t)dy & 15) == 0)

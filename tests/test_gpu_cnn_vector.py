@@ -1,0 +1,87 @@
+"""Vector form of the convolutions at the edges of its tiles (GPU).
+
+Channel counts that are multiples of 8 and aligned operands take the vector
+kernels; the same operands 8 bytes off alignment take the general ones.  Forward
+and input gradient add the same products in the same order, so the two must give
+the same bits, whatever the values.  The filter and bias gradients differ by the
+FP32 accumulation order only: 1e-5 of the sum of |terms| against FP64.
+"""
+import numpy as np
+import pytest
+
+from oracle import cnn_oracle as co
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # n, h, w, c, k, r, stride, pad
+    (7, 61, 59, 8, 68, 3, 1, 1),      # 64 and 4 channels per block, k = 72 of 96
+    (6, 131, 127, 24, 72, 1, 2, 0),   # blocks of all four classes, three without a tap
+    (6, 131, 127, 16, 64, 3, 2, 1),   # the same, classes of 1, 2, 2 and 4 taps
+    (6, 65, 67, 16, 24, 3, 2, 1),     # a class per workgroup
+    (2, 20, 21, 16, 8, 3, 4, 1),      # sixteen classes, seven of them without a tap
+    (3, 9, 7, 72, 40, 3, 1, 1),       # 16 channels per workgroup, N = 8 of 16 in the last
+    (1, 1, 1, 8, 8, 1, 1, 0),         # one pixel
+    (2, 5, 4, 480, 8, 3, 1, 1),       # filters of 16 channels do not fit: the general kernel
+]
+
+
+def _shifted(torch, t):
+    """A copy of t whose storage starts 8 bytes past a 16-byte boundary."""
+    off = 8 // t.element_size()
+    buf = torch.empty(t.numel() + off, dtype=t.dtype, device=t.device)
+    out = buf[off:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_vector_form_equals_the_general_one(shape, special):
+    import torch
+    from paper_2503_16424_amd import cnn
+    n, h, w, c, k, r, s, p = shape
+    g = torch.Generator().manual_seed(sum(shape))
+    d = cnn.conv_desc(n, h, w, c, k, r, s, p)
+
+    def bf16(*size):
+        return torch.randn(size, generator=g).to(torch.bfloat16)
+
+    x, wt, dy = bf16(n, h, w, c), bf16(k, r, r, c) * 0.2, torch.randn((n, d.ho, d.wo, k), generator=g)
+    bias = torch.randn(k, generator=g)
+    if special:
+        x.view(-1)[::97] = float("inf")
+        x.view(-1)[5::89] = float("nan")
+        dy.view(-1)[::101] = float("-inf")
+        dy.view(-1)[7::103] = float("nan")
+    xg, wg = x.view(torch.int16).cuda(), wt.view(torch.int16).cuda()
+    dyg, bg = dy.cuda(), bias.cuda()
+
+    def run(xg, wg, dyg, off):
+        like = (lambda t: _shifted(torch, t)) if off else (lambda t: t)
+        y = like(torch.zeros((n, d.ho, d.wo, k), device="cuda"))
+        yb = like(torch.zeros((n, d.ho, d.wo, k), dtype=torch.int16, device="cuda"))
+        dx = like(torch.zeros((n, h, w, c), device="cuda"))
+        dw, db = torch.empty((k, r, r, c), device="cuda"), torch.empty(k, device="cuda")
+        cnn.conv_fwd(d, xg, wg, bg, relu=False, y=y)
+        cnn.conv_fwd(d, xg, wg, bg, relu=True, y_bf16=yb)
+        cnn.conv_bwd_data(d, dyg, wg, dx, x_mask=xg)
+        cnn.conv_bwd_weight(d, dyg, xg, dw, db)
+        return [t.cpu() for t in (y, yb, dx, dw, db)]
+
+    fast = run(xg, wg, dyg, False)
+    slow = run(*(_shifted(torch, t) for t in (xg, wg, dyg)), True)
+    for a, b in zip(fast[:3], slow[:3]):
+        if a.dtype == torch.int16:
+            a, b = a.view(torch.bfloat16), b.view(torch.bfloat16)
+        a, b = a.float().numpy(), b.float().numpy()
+        assert np.array_equal(a, b, equal_nan=True)
+    if special:
+        for a, b in zip(fast[3:], slow[3:]):
+            assert torch.equal(a.isnan(), b.isnan())
+        return
+    x64, dyb = x.double().numpy(), co.bf16(dy.numpy())
+    ref, _ = co.conv_bwd_weight(dyb, x64, r, s, p)
+    scale, _ = co.conv_bwd_weight(np.abs(dyb), np.abs(x64), r, s, p)
+    assert (np.abs(fast[3].numpy() - ref) / (scale + 1e-30)).max() <= 1e-5
+    d64 = dy.double().numpy().reshape(-1, k)
+    assert (np.abs(fast[4].numpy() - d64.sum(0)) / np.abs(d64).sum(0)).max() <= 1e-5
