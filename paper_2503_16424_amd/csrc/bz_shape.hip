@@ -11,7 +11,8 @@
 // stable LSD radix sort on the float bits of the non-negative areas, the
 // binning's sort kernels; for a batch a second stable pass on the canvas
 // index keeps every canvas's curves together), then the first Gaussian of
-// every draw position by an exclusive scan of the per-curve Gaussian counts.  Everything stays on
+// every draw position by an exclusive scan of the per-curve Gaussian counts; up to
+// 4096 curves all that is one workgroup's work.  Everything stays on
 // the device, so the order can follow the curves every step.
 //
 // Xing loss (Sec. 3.5, the convexity term of LIVE).  Per cubic segment
@@ -60,13 +61,16 @@ __global__ __launch_bounds__(64) void k_area(bz_curves c, float *__restrict__ ar
     if (lane == 0) area[i] = (float)(closed ? 0.5 * fabs(acc) : acc * (double)v.width);
 }
 
-// keys: float bits of the area (non-negative floats order as their bits;
-// NaN goes last), values: curve index.
+// Float bits of an area: non-negative floats order as their bits, NaN goes last.
+__device__ inline uint32_t area_key(float a) {
+    return isnan(a) ? 0xffffffffu : __float_as_uint(fmaxf(a, 0.f));
+}
+
+// keys: area keys, values: curve index.
 __global__ void k_area_keys(const float *area, int n, uint32_t *keys, uint32_t *vals) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float a = area[i];
-    keys[i] = isnan(a) ? 0xffffffffu : __float_as_uint(fmaxf(a, 0.f));
+    keys[i] = area_key(area[i]);
     vals[i] = (uint32_t)i;
 }
 
@@ -79,13 +83,99 @@ __global__ void k_canvas_keys(const bz_canvas *cv, int n_canvas, const uint32_t 
                                    [](const bz_canvas &r) { return (int64_t)r.curve_off; });
 }
 
+// Gaussians of curve i.
+__device__ inline uint32_t curve_gauss(const bz_curves &c, int i) {
+    const int rows = c.kind[i] == BZ_CLOSED ? c.r_interior[i] + 2 : 1;
+    return (uint32_t)(rows * c.k_samples[i]);
+}
+
 __global__ void k_order_counts(bz_curves c, const uint32_t *vals, int32_t *order, uint32_t *cnt) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= c.n_curves) return;
     const int i = (int)vals[p];
     order[p] = i;
-    const int rows = c.kind[i] == BZ_CLOSED ? c.r_interior[i] + 2 : 1;
-    cnt[p] = (uint32_t)(rows * c.k_samples[i]);
+    cnt[p] = curve_gauss(c, i);
+}
+
+// The whole order of up to kOrderMost curves in one workgroup: a bitonic sort in
+// LDS of (canvas, area key, curve) packed in 64 bits (all different, so ties end by
+// index as a stable sort leaves them), then the first Gaussian of each position by
+// a scan.  m: the power of two (at least 64) the list is filled up to, blockDim.x =
+// min(1024, max(64, m / 2)).  A wave's 64 pairs of a step of stride up to 64 lie in
+// 128 consecutive keys that no other wave touches: only longer strides need the
+// block's barrier.  Bound by the chain of steps (45 for 512 keys, 78 for 4096): 14 us
+// for 400 curves against 130 us for four radix passes of four launches each, the
+// counts and their scan.
+constexpr int kOrderMost = 4096;
+
+__device__ inline void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(1024) void k_order_small(bz_curves c, const bz_canvas *cv, int n_canvas,
+                                                      const float *area, int m, int32_t *order,
+                                                      int64_t *gauss_off) {
+    __shared__ uint64_t key[kOrderMost];
+    __shared__ uint64_t s_wave[16];
+    const int n = c.n_curves, t = threadIdx.x, nt = blockDim.x;
+    for (int i = t; i < m; i += nt) {
+        uint64_t k = ~0ull;                     // after every curve
+        if (i < n) {
+            const uint32_t canvas =
+                cv ? (uint32_t)batch_find(cv, n_canvas, (int64_t)i,
+                                          [](const bz_canvas &r) { return (int64_t)r.curve_off; })
+                   : 0u;
+            k = ((uint64_t)canvas << 48) | ((uint64_t)area_key(area[i]) << 16) | (uint64_t)i;
+        }
+        key[i] = k;
+    }
+    __syncthreads();
+    bool wide = false;                          // the step before crossed waves
+    for (int k = 2; k <= m; k <<= 1) {
+        for (int d = k >> 1; d > 0; d >>= 1) {
+            if (wide || d > 64) __syncthreads();
+            else wave_lds_order();
+            wide = d > 64;
+            for (int p = t; p < m / 2; p += nt) {
+                const int i = 2 * p - (p & (d - 1));
+                const uint64_t a = key[i], b = key[i + d];
+                if ((a > b) == ((i & k) == 0)) {
+                    key[i] = b;
+                    key[i + d] = a;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // per thread consecutive positions; the scan as in the binning
+    const int per = (m + nt - 1) / nt, p0 = t * per;
+    uint64_t sum = 0;
+    for (int q = 0; q < per && p0 + q < n; ++q) {
+        const int i = (int)(key[p0 + q] & 0xffffu);
+        order[p0 + q] = i;
+        sum += curve_gauss(c, i);
+    }
+    uint64_t incl = sum;
+    const int lane = t & 63, w = t >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t v = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += v;
+    }
+    if (lane == 63) s_wave[w] = incl;
+    __syncthreads();
+    uint64_t at = incl - sum, total = 0;
+    for (int i = 0; i < nt / 64; ++i) {
+        if (i < w) at += s_wave[i];
+        total += s_wave[i];
+    }
+    for (int q = 0; q < per && p0 + q < n; ++q) {
+        gauss_off[p0 + q] = (int64_t)at;
+        at += curve_gauss(c, (int)(key[p0 + q] & 0xffffu));
+    }
+    if (t == 0) gauss_off[n] = (int64_t)total;
 }
 
 __global__ void k_widen(const uint32_t *offs, int n, int64_t *gauss_off) {
@@ -198,6 +288,14 @@ hipError_t launch_area_order(const bz_curves &c, const bz_batch *batch, float *a
     uint64_t *part = (uint64_t *)(w + L.part);
     int64_t *status = (int64_t *)(w + L.status);
     hipLaunchKernelGGL(k_area, dim3(n), dim3(64), 0, s, c, area);
+    if (n <= kOrderMost && (!batch || batch->n_canvas <= 65536)) {
+        int m = 64;
+        while (m < n) m *= 2;
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(m < 128 ? 64 : m > 2048 ? 1024 : m / 2), 0, s,
+                           c, batch ? batch->canvas : nullptr, batch ? batch->n_canvas : 0,
+                           (const float *)area, m, order, gauss_off);
+        return hipGetLastError();
+    }
     const unsigned nb = (unsigned)cdiv(n, 256);
     hipLaunchKernelGGL(k_area_keys, dim3(nb), dim3(256), 0, s, (const float *)area, n, keys, vals);
     hipError_t e = sort_pairs_u32(keys, vals, keys2, vals2, n, 32, hist, part, status, s);

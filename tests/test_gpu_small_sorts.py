@@ -1,0 +1,89 @@
+"""One-workgroup scans and sorts at the sizes where they change over (GPU).
+
+Draw order: up to 4096 curves are sorted in one workgroup, more by radix passes;
+both must give numpy's stable order of the float keys (ties by index, NaN last).
+Tile lists: up to 512 radix blocks (from the pair buffer's size), or 64 per bucket,
+each bucket's digit counts are scanned by one workgroup, above that by the
+device-wide scan; the lists of a frame do not depend on the buffer's size, and an overflow leaves every
+range empty.  All whole numbers: compared exactly.
+"""
+import numpy as np
+import pytest
+
+from paper_2503_16424_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+KEY_BLOCK = 4096            # pairs per radix block
+
+
+def _repeated(n, seed, nan=False):
+    """n open strokes of 7 different shapes (many equal areas)."""
+    sc = scenes.uniform_open(seed, 64, 48, n, 8)
+    pts = sc.ctrl.reshape(n, -1, 2)
+    pts[:] = pts[np.arange(n) % 7 % n]
+    sc.ctrl = pts.reshape(sc.ctrl.shape)
+    sc.stroke_w[:] = sc.stroke_w[np.arange(n) % 7 % n]
+    if nan:
+        sc.ctrl.reshape(n, -1, 2)[n // 2, 0, 0] = np.nan
+    return sc
+
+
+@pytest.mark.parametrize("nan", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 2048, 2049, 4096, 4097])
+def test_order_of_n_curves(n, nan):
+    from paper_2503_16424_amd import bz
+    sc = _repeated(n, 40 + n, nan)
+    r = bz.Rasterizer(sc, draw_order="area")
+    r.order.fill_(-1)
+    r.reorder()
+    area = r.area.cpu().numpy()[:n]
+    assert np.isnan(area).sum() == int(nan)
+    keys = np.where(np.isnan(area), np.inf, area)
+    order = np.argsort(keys, kind="stable")
+    assert np.array_equal(r.order.cpu().numpy()[:n], order)
+    per = np.where(sc.kind == 1, sc.r_interior + 2, 1) * sc.k_samples
+    assert np.array_equal(r.gauss_off.cpu().numpy(), np.concatenate([[0], np.cumsum(per[order])]))
+
+
+@pytest.mark.parametrize("counts", [(64, 1, 63), (2048, 2000, 48), (2048, 2000, 49)])
+def test_order_of_a_batch(counts):
+    from paper_2503_16424_amd import bz
+    parts = [_repeated(n, 7) for n in counts]        # the same shapes in every canvas
+    r = bz.Rasterizer(parts, draw_order="area")
+    r.reorder()
+    n = sum(counts)
+    area = r.area.cpu().numpy()[:n]
+    canvas = np.repeat(np.arange(len(counts)), counts)
+    order = np.lexsort((np.arange(n), area, canvas))
+    assert np.array_equal(r.order.cpu().numpy()[:n], order)
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8)])
+def test_lists_do_not_depend_on_the_buffer(tile):
+    import torch
+    from paper_2503_16424_amd import bz
+    sc = scenes.mixed(5, 500, 300, 20, 30, K=24, R=10, S_open=3, extent=(4.0, 200.0))
+    r = bz.Rasterizer(sc, bz.RenderOptions(tile_w=tile[0], tile_h=tile[1]))
+    n_tiles = -(-500 // tile[0]) * -(-300 // tile[1])
+    buckets = -(-n_tiles // 256)
+    lists = []
+    most = max(512, 64 * buckets)
+    for blocks in (most, most + 1):
+        cap = (blocks - buckets) * KEY_BLOCK
+        r._alloc_pairs(cap)
+        r.ids.fill_(-1)
+        r.ranges.fill_(-1)
+        r.sample()
+        r.bin()
+        assert r.pairs_required() <= cap
+        lists.append((r.ranges.clone(), r.ids[: r.pairs_required()].clone()))
+    assert torch.equal(lists[0][0], lists[1][0]) and torch.equal(lists[0][1], lists[1][1])
+    rg = lists[0][0].view(-1, 2).cpu().numpy().astype(np.int64)
+    assert (rg[:, 1] - rg[:, 0]).sum() == r.pairs_required() > 1000
+    r._alloc_pairs(1000)
+    r.ranges.fill_(-1)
+    r.sample()
+    r.bin()
+    assert r.flags() & bz.STATUS_OVERFLOW
+    assert not r.ranges.any()
