@@ -123,14 +123,11 @@ struct TileArgs {
 // minus m'.
 // - With u0 = e' . m' and w0 = f x m' staged, u = e' . l - u0 and
 //   w = f x l - w0 cost two FMAs each and no offsets.
-// - The reverse pass stages the same form relative to the tile centre (the
-//   origin the per-tile sums of every quad share), with l the pixel centre
-//   from it.  The conic gradient of entries past the tile's sum table needs
-//   the offset d itself: d = M^-1 (u, w), M = [e'.x e'.y; -f.y f.x], whose
-//   determinant e' . f = k |e'|^2 the record gives; 1 / det is staged.
+// - The reverse pass stages the same form relative to the tile centre, with l
+//   the pixel centre from it.
 struct Staged {
     float4 m;   // -u0, -w0, e'.x, e'.y
-    float4 q;   // f.x, f.y, 1 / (e' . f) (reverse pass), o' = o / (1 - g_min)
+    float4 q;   // f.x, f.y, k, o' = o / (1 - g_min)
     float4 c;   // r, g, b, o' * g_min
 };
 
@@ -138,10 +135,9 @@ struct Staged {
 constexpr float kHalfLog2eSqrt = 0.84932180028801907f;
 
 // Load a record and compute its LDS constants.  q receives the record's shape
-// (e.x, e.y, k, o).
-template <bool kSweep>
+// (e.x, e.y, k, o), mean the relative mean m'.
 __device__ inline void stage_record(const TileArgs &a, uint32_t id, float qx0, float qy0,
-                                    Staged &st, float4 &q) {
+                                    Staged &st, float4 &q, float2 &mean) {
     const float4 m = a.rec[3 * (int64_t)id];
     q = a.rec[3 * (int64_t)id + 1];
     const float4 c = a.rec[3 * (int64_t)id + 2];
@@ -152,32 +148,30 @@ __device__ inline void stage_record(const TileArgs &a, uint32_t id, float qx0, f
     const float nu0 = -fmaf(ex, mx, ey * my);      // -(e' . m')
     const float nw0 = -fmaf(fx, my, -fy * mx);     // -(f x m')
     st.m = make_float4(nu0, nw0, ex, ey);
-    st.q = make_float4(fx, fy, kSweep ? 0.f : 1.f / fmaf(ex, fx, ey * fy), op);
+    st.q = make_float4(fx, fy, q.z, op);
     st.c = make_float4(c.x, c.y, c.z, op * a.g_min);
+    mean = make_float2(mx, my);
 }
 
 // Load a tile-list entry, compute its LDS constants and test its support
 // against the wave's 8x8 quad (first pixel centre qx0, qy0).
-template <bool kSweep>
 __device__ inline bool stage_entry(const TileArgs &a, uint32_t id, float qx0, float qy0,
                                    Staged &st) {
     float4 q;
-    stage_record<kSweep>(a, id, qx0, qy0, st, q);
+    float2 m;
+    stage_record(a, id, qx0, qy0, st, q, m);
     // offsets of the quad's first pixel centre from the mean
-    const float4 m = a.rec[3 * (int64_t)id];
-    const float x0 = -((m.x - qx0) + m.z), y0 = -((m.y - qy0) + m.w);
+    const float x0 = -m.x, y0 = -m.y;
     float qxx, qxy, qyy;
     shape_conic(q.x, q.y, q.z, qxx, qxy, qyy);
     return box_hit(x0, x0 + 7.f, y0, y0 + 7.f, qxx, qxy, qyy, a.box_thr);
 }
 
-// stage_entry for the reverse pass: the record staged relative to the tile
-// centre (ox, oy), the quad's first pixel centre at (bx, by) from it.
-__device__ inline bool stage_entry_bwd(const TileArgs &a, uint32_t id, float ox, float oy,
-                                       float bx, float by, Staged &st) {
-    float4 q;
-    stage_record<false>(a, id, ox, oy, st, q);
-    const float4 m = a.rec[3 * (int64_t)id];
+// The test of stage_entry with the mean relative to the tile centre (ox, oy), the
+// quad's first pixel centre at (bx, by) from it.
+__device__ inline bool entry_hit_bwd(const TileArgs &a, uint32_t id, float ox, float oy, float bx,
+                                     float by) {
+    const float4 m = a.rec[3 * (int64_t)id], q = a.rec[3 * (int64_t)id + 1];
     const float x0 = bx - ((m.x - ox) + m.z), y0 = by - ((m.y - oy) + m.w);
     float qxx, qxy, qyy;
     shape_conic(q.x, q.y, q.z, qxx, qxy, qyy);
@@ -185,18 +179,11 @@ __device__ inline bool stage_entry_bwd(const TileArgs &a, uint32_t id, float ox,
 }
 
 // Base-2 exponent p2 = (e' . d)^2 + (f x d)^2 of a staged entry at the
-// pixel centre (lx, ly) from the staging origin; u = e' . d and w = f x d are
-// returned for the gradient.
-__device__ inline float exponent2(const Staged &st, float lx, float ly, float &u, float &w) {
-    u = fmaf(st.m.z, lx, fmaf(st.m.w, ly, st.m.x));
-    w = fmaf(st.q.x, ly, fmaf(-st.q.y, lx, st.m.y));
+// pixel centre (lx, ly) from the staging origin.
+__device__ inline float exponent2(const Staged &st, float lx, float ly) {
+    const float u = fmaf(st.m.z, lx, fmaf(st.m.w, ly, st.m.x));
+    const float w = fmaf(st.q.x, ly, fmaf(-st.q.y, lx, st.m.y));
     return fmaf(u, u, w * w);
-}
-
-// The same without u and w (the front-to-back sweep).
-__device__ inline float exponent2_sweep(const Staged &st, float lx, float ly) {
-    float u, w;
-    return exponent2(st, lx, ly, u, w);
 }
 
 // Word of the visit mask of batch k of tile t inside one quad plane: tile t's
@@ -280,15 +267,6 @@ __device__ inline float select_lanes(uint64_t m, float on, float off) {
 }
 __device__ inline uint32_t select_lanes_u32(uint64_t m, uint32_t on, uint32_t off) {
     return __float_as_uint(select_lanes(m, __uint_as_float(on), __uint_as_float(off)));
-}
-
-// The backward's quad origin, re-read from LDS at every staging so that it
-// occupies no register across the slot loop: the index is a zero the compiler
-// cannot see through (one scalar move), so the read is not hoisted.
-__device__ inline int opaque_zero() {
-    int z;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-    return z;
 }
 
 // Clear bit b of a wave-uniform mask: one scalar instruction (the compiler's
@@ -375,7 +353,7 @@ __device__ inline Sweep fwd_sweep(const TileArgs &a, Staged *my, uint32_t start,
         bool hit = false;
         if (j < end) {
             Staged st;
-            hit = stage_entry<true>(a, a.ids[j], qx0, qy0, st);
+            hit = stage_entry(a, a.ids[j], qx0, qy0, st);
             my[lane] = st;
         }
         uint64_t mask = __ballot(hit);
@@ -387,7 +365,7 @@ __device__ inline Sweep fwd_sweep(const TileArgs &a, Staged *my, uint32_t start,
             const int b = __builtin_ctzll(mask);
             clear_bit(mask, b);
             const Staged st = read_staged_at(staged_off(my_off, b));
-            const float G = __builtin_amdgcn_exp2f(-exponent2_sweep(st, lx, ly));
+            const float G = __builtin_amdgcn_exp2f(-exponent2(st, lx, ly));
             // contributors: inside the support and not stopped, as a lane mask
             const uint64_t cm = __builtin_amdgcn_ballot_w64(G > g_min) & ~stopped;
             const float araw = fmaf(st.q.w, G, -st.c.w);
@@ -623,7 +601,7 @@ __device__ inline float min_f32(float a, float b) {
 //    four lanes, where one lane per pixel needs a reduction over 64 lanes for
 //    each slot (100 of 287 cycles a slot in that form).
 constexpr int kGroup = 16;
-// Staged rows of a slot: -u0, e'.x, e'.y | -w0, -f.y, f.x | r, g, b | o', -o' g_min
+// Staged rows of a slot: -u0, e'.x, e'.y, -w0, k | o' | r, g, b | m'.x, m'.y
 constexpr int kStageRows = 11;
 
 // A wave's LDS.  The recomputing form's front-to-back sweep stages its 64
@@ -649,30 +627,21 @@ constexpr int kSums = 10;     // sums over pixels of one Gaussian
 //     A = e'.x^2 + f.y^2, B = e'.x e'.y - f.x f.y, C = e'.y^2 + f.x^2;
 //   dL/dQ = -P (dx^2 / 2, dx dy, dy^2 / 2);  dL/do = f (G - g_min) / (1 - g_min);
 //   dL/dcolour = alpha T g.
-// The sums are moments about the tile centre: with (x, y) the pixel centre
-// relative to it, sums 0-9 are f G (1, x, y, x^2, xy, y^2), alpha T g (3) and
-// f; planes_of turns them into the planes with the record's mean and shape
-// (sum(f G dx) = sum(f G x) - mx sum(f G), ...).
-__device__ inline void planes_of(const TileArgs &a, uint32_t id, const float (&S)[kSums], float ox,
-                                 float oy, float (&out)[kGradPlanes]) {
-    const float4 m = a.rec[3 * (int64_t)id];
+// Sums 0-9 are f G (1, dx, dy, dx^2, dx dy, dy^2), alpha T g (3) and f;
+// planes_of turns them into the planes with the record's shape.
+__device__ inline void planes_of(const TileArgs &a, uint32_t id, const float (&S)[kSums],
+                                 float (&out)[kGradPlanes]) {
     const float4 q = a.rec[3 * (int64_t)id + 1];
-    const float mx = (m.x - ox) + m.z, my = (m.y - oy) + m.w;   // mean - tile centre
     const float ex = kHalfLog2eSqrt * q.x, ey = kHalfLog2eSqrt * q.y;
     const float fx = q.z * ex, fy = q.z * ey;
     const float op = q.w * a.inv_1mg;
-    // sums of f G (dx, dy, dx^2, dx dy, dy^2), d = pixel - mean
-    const float sx = fmaf(-mx, S[0], S[1]), sy = fmaf(-my, S[0], S[2]);
-    const float sxx = fmaf(-mx, S[1] + sx, S[3]);
-    const float sxy = fmaf(-mx, sy, fmaf(-my, S[1], S[4]));
-    const float syy = fmaf(-my, S[2] + sy, S[5]);
     const float A = fmaf(ex, ex, fy * fy), B = fmaf(ex, ey, -fx * fy), C = fmaf(ey, ey, fx * fx);
     const float k2 = 1.38629436112f * op;        // 2 ln 2 o'
-    out[0] = k2 * fmaf(A, sx, B * sy);
-    out[1] = k2 * fmaf(B, sx, C * sy);
-    out[2] = -0.5f * op * sxx;
-    out[3] = -op * sxy;
-    out[4] = -0.5f * op * syy;
+    out[0] = k2 * fmaf(A, S[1], B * S[2]);
+    out[1] = k2 * fmaf(B, S[1], C * S[2]);
+    out[2] = -0.5f * op * S[3];
+    out[3] = -op * S[4];
+    out[4] = -0.5f * op * S[5];
     out[5] = fmaf(-a.g_min, S[9], S[0]) * a.inv_1mg;
     out[6] = S[6];
     out[7] = S[7];
@@ -762,9 +731,9 @@ struct BwdLane {
 __device__ inline void bwd_group(BwdWave &wl, int s, int q, bool last, bool check,
                                  const BwdLane &L, float (&out)[3]) {
     const float nu0 = wl.rec[0][s], ex = wl.rec[1][s], ey = wl.rec[2][s];
-    const float nw0 = wl.rec[3][s], mfy = wl.rec[4][s], fx = wl.rec[5][s];
+    const float nw0 = wl.rec[3][s], k = wl.rec[4][s], mfy = -(k * ey), fx = k * ex;
     const float cr = wl.rec[6][s], cgr = wl.rec[7][s], cb = wl.rec[8][s];
-    const float op = wl.rec[9][s], mog = wl.rec[10][s];
+    const float op = wl.rec[5][s], mog = -(op * L.g_min);
     const uint32_t pos = wl.pos[s];
     float wx[4];
 #pragma unroll
@@ -854,8 +823,10 @@ __device__ inline void bwd_group(BwdWave &wl, int s, int q, bool last, bool chec
         asm volatile("" : "+v"(S0), "+v"(Sr), "+v"(Srr), "+v"(Sb), "+v"(Srb), "+v"(Sbb), "+v"(Sf),
                      "+v"(Sc0), "+v"(Sc1), "+v"(Sc2));
     }
-    // moments about the tile centre: x = x[0] + r, y = y[0] + 2 b
-    const float X0 = L.x[0], Y0 = L.y[0];
+    // moments about the mean: dx = x[0] - m'.x + r, dy = y[0] - m'.y + 2 b.  Where f G
+    // is not small the lane is near the mean; about the tile centre the moments of a
+    // small Gaussian lose (8 / sigma)^2 of their precision when they are moved.
+    const float X0 = L.x[0] - wl.rec[9][s], Y0 = L.y[0] - wl.rec[10][s];
     float v[10];
     v[0] = S0;
     v[1] = fmaf(X0, S0, Sr);
@@ -1017,11 +988,7 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
             if (kRecompute && kbox > kVisCap) {
                 --kbox;
                 const uint32_t p = 64 * kbox + (uint32_t)lane;
-                bool hit = false;
-                if (p < len) {
-                    Staged st;
-                    hit = stage_entry_bwd(a, a.ids[start + p], ox, oy, bx, by, st);
-                }
+                const bool hit = p < len && entry_hit_bwd(a, a.ids[start + p], ox, oy, bx, by);
                 push(kbox, __ballot(hit));
                 continue;
             }
@@ -1047,10 +1014,11 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
         // stage the first n: lane l slot l, the slots past them contribute nothing
         {
             float4 sm = make_float4(0.f, 0.f, 0.f, 0.f), sq = sm, sc = sm;
+            float2 mean = make_float2(0.f, 0.f);
             if (lane < n) {
                 Staged st;
                 float4 shape;
-                stage_record<true>(a, a.ids[start + wl.pos[lane]], ox, oy, st, shape);
+                stage_record(a, a.ids[start + wl.pos[lane]], ox, oy, st, shape, mean);
                 sm = st.m;
                 sq = st.q;
                 sc = st.c;
@@ -1059,13 +1027,13 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
             wl.rec[1][lane] = sm.z;
             wl.rec[2][lane] = sm.w;
             wl.rec[3][lane] = sm.y;
-            wl.rec[4][lane] = -sq.y;
-            wl.rec[5][lane] = sq.x;
+            wl.rec[4][lane] = sq.z;
+            wl.rec[5][lane] = sq.w;
             wl.rec[6][lane] = sc.x;
             wl.rec[7][lane] = sc.y;
             wl.rec[8][lane] = sc.z;
-            wl.rec[9][lane] = sq.w;
-            wl.rec[10][lane] = -sc.w;
+            wl.rec[9][lane] = mean.x;
+            wl.rec[10][lane] = mean.y;
         }
         wave_lds_sync();
         for (int s0 = 0; s0 < n; s0 += kGroup) {
@@ -1094,7 +1062,7 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
 #pragma unroll
                         for (int v = 0; v < kSums; ++v) S[v] = wl.rec[v][s];
                         id = a.ids[start + p];
-                        planes_of(a, id, S, ox, oy, o);
+                        planes_of(a, id, S, o);
 #pragma unroll
                         for (int v = 0; v < kGradPlanes; ++v) wl.rec[v][s] = o[v];
                     }
@@ -1126,7 +1094,7 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
         uint32_t id = kNoGauss;
         if (any) {
             id = a.ids[start + p];
-            planes_of(a, id, S, ox, oy, o);
+            planes_of(a, id, S, o);
 #pragma unroll
             for (int v = 0; v < kGradPlanes; ++v) wl.rec[v][lane] = o[v];
         }
