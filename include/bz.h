@@ -409,6 +409,36 @@ bz_status bz_xing_loss(const bz_curves *c, float weight, float *loss, float *d_c
 bz_status bz_l2_grad(const float *image, const float *target, int64_t n, float scale,
                      float *d_image, float *loss, hipStream_t stream);
 
+/* One array of an Adam step (Sec. 3.5): n parameters with their moments, and d, the
+ * gradient before the chain factor (scale_even for even indices, scale_odd for odd
+ * ones: x and y of interleaved points; 1 for none).  With g = d * scale (written to
+ * grad unless that is NULL):
+ *   m += one_minus_beta1 (g - m);   v = beta2 v + one_minus_beta2 g^2;
+ *   param -= step_size m / (sqrt(v) / bias2_sqrt + eps), then kept in [lo, hi]
+ * (a NaN stays).  step_size = lr / (1 - beta1^t), bias2_sqrt = sqrt(1 - beta2^t). */
+typedef struct {
+    float *param, *m, *v, *grad;
+    const float *d;
+    int64_t n;
+    float scale_even, scale_odd;
+    float one_minus_beta1, beta2, one_minus_beta2, eps, step_size, bias2_sqrt;
+    float lo, hi;
+} bz_adam_group;
+
+/* Adam step of up to 8 arrays (device, FP32, none overlapping) in one launch. */
+bz_status bz_adam_step(const bz_adam_group *groups, int32_t n_groups, hipStream_t stream);
+
+/* dst = (src + add) * scale of one array, the scales as in bz_adam_group. */
+typedef struct {
+    float *dst;
+    const float *src;
+    int64_t n;
+    float add, scale_even, scale_odd;
+} bz_affine_group;
+
+/* Up to 8 such arrays in one launch: optimised parameters to curve parameters. */
+bz_status bz_affine_copy(const bz_affine_group *groups, int32_t n_groups, hipStream_t stream);
+
 /* Short description of a status code (static string). */
 const char *bz_status_str(bz_status s);
 

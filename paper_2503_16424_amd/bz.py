@@ -72,12 +72,26 @@ class Grads(C.Structure):
                 ("d_opacity", C.c_void_p), ("d_gauss", C.c_void_p)]
 
 
+class AdamGroup(C.Structure):
+    _fields_ = [("param", C.c_void_p), ("m", C.c_void_p), ("v", C.c_void_p),
+                ("grad", C.c_void_p), ("d", C.c_void_p), ("n", C.c_int64)] + [
+                    (k, C.c_float) for k in ("scale_even", "scale_odd", "one_minus_beta1", "beta2",
+                                             "one_minus_beta2", "eps", "step_size", "bias2_sqrt",
+                                             "lo", "hi")]
+
+
+class AffineGroup(C.Structure):
+    _fields_ = [("dst", C.c_void_p), ("src", C.c_void_p), ("n", C.c_int64), ("add", C.c_float),
+                ("scale_even", C.c_float), ("scale_odd", C.c_float)]
+
+
 EXPORTS = ("bz_layout_host", "bz_workspace_size", "bz_num_tiles", "bz_batch_layout",
            "bz_visit_words", "bz_sample", "bz_sample_bin", "bz_bin",
            "bz_render_fwd", "bz_render_fwd_l2", "bz_render_bwd", "bz_render_bwd_gauss", "bz_render_bwd_curves",
            "bz_curve_area", "bz_area_order_workspace", "bz_area_order", "bz_xing_loss",
            "bz_l2_grad", "bz_status_str", "bz_peak_run", "bz_peak_work",
-           "bz_sample_bin_static", "bz_bwd_scratch_size", "bz_render_bwd_scratch")
+           "bz_sample_bin_static", "bz_bwd_scratch_size", "bz_render_bwd_scratch",
+           "bz_adam_step", "bz_affine_copy")
 
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024   # BZ_STATIC_SCRATCH_BYTES of bz.h
 
@@ -147,6 +161,10 @@ def load_library(path: str = LIB_PATH):
     lib.bz_l2_grad.restype = C.c_int
     lib.bz_l2_grad.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_float, C.c_void_p,
                                C.c_void_p, C.c_void_p]
+    lib.bz_adam_step.restype = C.c_int
+    lib.bz_adam_step.argtypes = [P(AdamGroup), C.c_int32, C.c_void_p]
+    lib.bz_affine_copy.restype = C.c_int
+    lib.bz_affine_copy.argtypes = [P(AffineGroup), C.c_int32, C.c_void_p]
     lib.bz_peak_run.restype = C.c_int
     lib.bz_peak_run.argtypes = [C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_int64,
                                 C.c_void_p]

@@ -22,6 +22,7 @@ from dataclasses import dataclass, field
 
 import numpy as np
 import torch
+import torch.optim.optimizer as torch_optimizer
 
 from . import bz
 
@@ -89,12 +90,58 @@ class FitResult:
     regrown: int = 0                                # pair-buffer growths during the loop
 
 
+def _plain(first, *others) -> bool:
+    """Dense FP32 tensors of one size on the device of the library's launches."""
+    return all(t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()
+               and t.numel() == first.numel() and t.device.index == torch.cuda.current_device()
+               for t in (first, *others))
+
+
+def _plain_adam(opt, params) -> bool:
+    """torch.optim.Adam over ``params``, one group each, with default options apart
+    from learning rate, betas and eps, and a step nobody has wrapped or hooked."""
+    if type(opt) is not torch.optim.Adam or "step" in vars(opt):
+        return False
+    if len(opt.param_groups) != len(params):
+        return False
+    for g, p in zip(opt.param_groups, params):
+        if len(g["params"]) != 1 or g["params"][0] is not p:
+            return False
+        if g["weight_decay"] != 0 or any(g.get(k) for k in ("amsgrad", "maximize", "capturable",
+                                                           "differentiable", "foreach", "fused")):
+            return False
+        if g.get("foreach") is not None or not all(
+                isinstance(v, float) for v in (g["lr"], g["eps"], *g["betas"])):
+            return False
+    return not _hooked(opt)
+
+
+def _hooked(opt) -> bool:
+    """Whether a hook waits for the optimiser's step (unknown: yes)."""
+    own = [vars(opt).get(k) for k in ("_optimizer_step_pre_hooks", "_optimizer_step_post_hooks")]
+    glob = [getattr(torch_optimizer, k, None)
+            for k in ("_global_optimizer_pre_hooks", "_global_optimizer_post_hooks")]
+    return any(h is None or len(h) > 0 for h in own + glob)
+
+
+def _library(name: str, groups) -> None:
+    arr = (type(groups[0]) * len(groups))(*groups)
+    bz._check(name, getattr(bz.load_library(), name)(arr, len(groups), bz._stream()))
+
+
+def _written(tensors) -> None:
+    """Tell autograd that the library wrote to these tensors."""
+    for t in tensors:
+        torch.autograd.graph.increment_version(t)
+
+
 class Fitter:
     """Parameters, optimiser and rasterizer of one optimisation."""
 
     def __init__(self, rast: "bz.Rasterizer", cfg: FitConfig | None = None):
         self.rast, self.cfg = rast, cfg or FitConfig()
-        self.half = torch.tensor([rast.W / 2.0, rast.H / 2.0], device=rast.dev)
+        self._half = (rast.W / 2.0, rast.H / 2.0)
+        self.half = torch.tensor(self._half, device=rast.dev)
         self.ctrl_n = torch.nn.Parameter(rast.ctrl / self.half - 1.0)
         self.color = torch.nn.Parameter(rast.color.clone())
         self.opacity = torch.nn.Parameter(rast.opacity.clone())
@@ -111,8 +158,22 @@ class Fitter:
         else:
             raise ValueError(f"unknown optimizer {c.optimizer!r}")
 
+    def _arrays(self):
+        """(parameter, curve buffer, its gradient) of every optimised array."""
+        r = self.rast
+        return ((self.ctrl_n, r.ctrl, r.d_ctrl), (self.color, r.color, r.d_color),
+                (self.opacity, r.opacity, r.d_opacity), (self.width, r.stroke_w, r.d_width))
+
     def push(self):
         """Parameters -> the rasterizer's curve buffers."""
+        arrays = self._arrays()
+        if all(_plain(p, dst) for p, dst, _ in arrays):
+            hx, hy = self._half
+            _library("bz_affine_copy", [
+                bz.AffineGroup(dst.data_ptr(), p.data_ptr(), p.numel(), *a)
+                for (p, dst, _), a in zip(arrays, ((1.0, hx, hy),) + ((0.0, 1.0, 1.0),) * 3)])
+            _written(dst for _, dst, _ in arrays)
+            return
         with torch.no_grad():
             self.rast.set_params(ctrl=(self.ctrl_n + 1.0) * self.half, color=self.color,
                                  opacity=self.opacity, stroke_w=self.width)
@@ -121,6 +182,8 @@ class Fitter:
         """One optimiser step from the rasterizer's last backward, then the
         box constraints (colours and opacities in [0, 1], widths >= min)."""
         r = self.rast
+        if self._update_in_one_launch():
+            return
         self.ctrl_n.grad = r.d_ctrl * self.half
         self.color.grad = r.d_color.clone()
         self.opacity.grad = r.d_opacity.clone()
@@ -130,6 +193,41 @@ class Fitter:
             self.color.clamp_(0.0, 1.0)
             self.opacity.clamp_(0.0, 1.0)
             self.width.clamp_(min=self.cfg.min_width)
+
+    def _update_in_one_launch(self) -> bool:
+        """update() by one kernel for torch's plain Adam with its state in place:
+        every other optimiser, option, layout or hook takes torch's own step (which
+        also makes the state, so the first update does), and so does a recording
+        graph, whose step counts torch keeps on the host."""
+        arrays = self._arrays()
+        if not (_plain_adam(self.opt, [p for p, _, _ in arrays])
+                and all(_plain(p, d) for p, _, d in arrays)):
+            return False
+        state = [self.opt.state.get(p, {}) for p, _, _ in arrays]
+        for (p, _, _), st in zip(arrays, state):
+            if set(st) != {"step", "exp_avg", "exp_avg_sq"}:
+                return False
+            t = st["step"]
+            if not (torch.is_tensor(t) and t.device.type == "cpu" and t.numel() == 1
+                    and _plain(p, st["exp_avg"], st["exp_avg_sq"])):
+                return False
+        if torch.cuda.is_current_stream_capturing():
+            return False
+        box = ((-math.inf, math.inf), (0.0, 1.0), (0.0, 1.0), (self.cfg.min_width, math.inf))
+        groups, written = [], []
+        for i, ((p, _, d), st, g) in enumerate(zip(arrays, state, self.opt.param_groups)):
+            st["step"] += 1
+            t, (b1, b2) = float(st["step"]), g["betas"]
+            p.grad = torch.empty_like(p)
+            scale = (1.0, 1.0) if i else self._half
+            groups.append(bz.AdamGroup(
+                p.data_ptr(), st["exp_avg"].data_ptr(), st["exp_avg_sq"].data_ptr(),
+                p.grad.data_ptr(), d.data_ptr(), p.numel(), *scale, 1.0 - b1, b2, 1.0 - b2,
+                g["eps"], g["lr"] / (1.0 - b1 ** t), math.sqrt(1.0 - b2 ** t), *box[i]))
+            written += [p, st["exp_avg"], st["exp_avg_sq"]]
+        _library("bz_adam_step", groups)
+        _written(written)
+        return True
 
     def state_arrays(self, step: int) -> dict:
         """Everything a resumed run needs, as host arrays: the step reached,
