@@ -1015,28 +1015,32 @@ __device__ inline int seg_find(const uint32_t *P, int nbk, uint32_t b) {
 }
 
 // A radix block of the in-bucket pass: its segment, its first element and
-// count, and the index of its digit-0 count in hseg.
+// count, and where its digit counts are in hseg: [block][digit] where each bucket
+// is scanned by itself (alone), bucket by bucket [digit][block] for the device-wide
+// scan.
 struct SegBlock {
     uint32_t pos0, cnt;
     int64_t h0;        // hseg index of (segment, digit 0, this block)
-    uint32_t nbs;      // blocks of the segment (stride between digits)
+    uint32_t hs;       // stride between digits
     bool real;
 };
 
-__device__ inline SegBlock seg_block(const uint32_t *s_S, const uint32_t *s_P, int nbk, uint32_t b) {
+__device__ inline SegBlock seg_block(const uint32_t *s_S, const uint32_t *s_P, int nbk, uint32_t b,
+                                     bool alone) {
     SegBlock r;
     r.real = b < s_P[nbk];
     if (!r.real) {
-        r.pos0 = r.cnt = r.nbs = 0;
+        r.pos0 = r.cnt = 0;
+        r.hs = 1;
         r.h0 = (int64_t)b * kRadix;
         return r;
     }
     const int s = seg_find(s_P, nbk, b);
     const uint32_t j = b - s_P[s];
-    r.nbs = s_P[s + 1] - s_P[s];
     r.pos0 = s_S[s] + j * (uint32_t)kTile;
     r.cnt = min((uint32_t)kTile, s_S[s + 1] - r.pos0);
-    r.h0 = (int64_t)kRadix * s_P[s] + j;
+    r.hs = alone ? 1u : s_P[s + 1] - s_P[s];
+    r.h0 = alone ? (int64_t)kRadix * b : (int64_t)kRadix * s_P[s] + j;
     return r;
 }
 
@@ -1061,33 +1065,76 @@ __global__ __launch_bounds__(256) void k_seg_hist(const uint32_t *__restrict__ p
     load_seg(seg, nbk, s_S, s_P);
     h[t] = 0u;
     __syncthreads();
-    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x);
+    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x, alone);
     if (!sb.real && alone) return;             // uniform over the block
     // consecutive pairs of a bucket are mostly consecutive keys: no runs of
     // equal digits to add at once, so one LDS atomic per pair
     for (uint32_t i = t; i < sb.cnt; i += kBlk) atomicAdd(&h[packed[sb.pos0 + i] >> 24], 1u);
     __syncthreads();
-    hseg[sb.h0 + (int64_t)t * (sb.real ? sb.nbs : 1u)] = h[t];
+    hseg[sb.h0 + (int64_t)t * sb.hs] = h[t];
 }
 
-// Scan of one bucket's counts ([digit][radix block], which add up to its pairs)
-// from its first position: one workgroup per bucket, no sums across workgroups.
+// Positions of one bucket's (digit, radix block) parts from its first position, over
+// the counts in place: one workgroup per bucket, thread (part p, digit d) taking a
+// quarter of the blocks, 1 KiB rows at a time.  Counts laid out by block, not by digit:
+// there a radix block wrote its 256 counts into as many lines, shared with blocks on
+// other XCDs (7.2 M pairs: counts and scan 12.5 + 12.6 us that way, 9.1 + 9.8 this way).
+// Bound by latency: one read of up to 64 blocks' rows 4.0-4.7 us, the 10,000 blocks of a
+// 2048x2048 frame with 33.7 M pairs in 64 buckets 4.6 us (device-wide scan 10 + 9).
 __global__ __launch_bounds__(kOneThreads) void k_seg_scan(const uint32_t *__restrict__ seg, int nbk,
                                                           const int64_t *status, uint32_t *hseg) {
+    constexpr int kParts = kOneThreads / kRadix;
+    __shared__ uint32_t s_sum[kParts][kRadix];
+    __shared__ uint32_t s_wave[kRadix / 64];
     if (status[1] & Status::kOverflow) return;
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, d = threadIdx.x % kRadix, p = threadIdx.x / kRadix;
     const uint32_t P = seg[nbk + 1 + b], nbs = seg[nbk + 2 + b] - P;
-    uint32_t *h = hseg + (int64_t)kRadix * P;
-    one_scan(h, h, (int64_t)kRadix * nbs, seg[b]);
+    const uint32_t per = (nbs + kParts - 1) / kParts;
+    const uint32_t r0 = min(p * per, nbs), r1 = min(r0 + per, nbs);
+    uint32_t *h = hseg + (int64_t)kRadix * P + d;
+    uint32_t x[kItems], sum = 0;
+    for (uint32_t r = r0; r < r1; r += kItems) {
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) x[j] = r + j < r1 ? h[(int64_t)kRadix * (r + j)] : 0u;
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) sum += x[j];
+    }
+    s_sum[p][d] = sum;
+    __syncthreads();
+    uint32_t before = 0, total = 0;             // of digit d: the parts before p, all
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) {
+        const uint32_t v = s_sum[i][d];
+        if (i < p) before += v;
+        total += v;
+    }
+    uint32_t tot;                               // digits of this wave, in digit order
+    uint32_t at = wave_excl_scan(total, tot);
+    if (p == 0 && (d & 63) == 63) s_wave[d >> 6] = tot;
+    __syncthreads();
+    for (int i = 0; i < (d >> 6); ++i) at += s_wave[i];
+    at += seg[b] + before;
+    const bool held = per <= kItems;            // the counts are still in registers
+    for (uint32_t r = r0; r < r1; r += kItems) {
+        if (!held) {
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) x[j] = r + j < r1 ? h[(int64_t)kRadix * (r + j)] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            if (r + j < r1) h[(int64_t)kRadix * (r + j)] = at;
+            at += x[j];
+        }
+    }
 }
 
-// Whether each bucket's counts are scanned by one workgroup: 16,384 counts take a
-// round of 1.3 us, which 64 radix blocks per bucket are.  4.0 us against 9 for the
-// device-wide scan on a 128 x 128 frame, 4.5 against 19 at 13 M pairs in 64 buckets;
-// 12.6 against 11 in a batch whose canvases fill some buckets far more than others.
-// Up to 512 blocks in all the longest bucket cannot take more than 8 rounds.
+// Whether each bucket's counts are scanned by one workgroup, which takes two rounds of
+// about 1 us for every 64 of its radix blocks after the first 64: up to 128 blocks per
+// bucket on average (a batch whose canvases fill some buckets far more than others
+// 9.8 us against 11), and up to 512 in all, where the longest bucket cannot take
+// more than 16.
 inline bool seg_alone(const BinLayout &L) {
-    return L.seg_blocks <= 512 || L.seg_blocks <= 64 * L.n_buckets;
+    return L.seg_blocks <= 512 || L.seg_blocks <= 128 * L.n_buckets;
 }
 
 // The in-bucket pass's scatter: ranks as in k_radix_scatter (digit = key
@@ -1099,7 +1146,8 @@ inline bool seg_alone(const BinLayout &L) {
 __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict__ packed,
                                                      const uint32_t *__restrict__ seg, int nbk,
                                                      const uint32_t *__restrict__ hseg,
-                                                     const int64_t *status, uint32_t n_tiles,
+                                                     const int64_t *status, bool alone,
+                                                     uint32_t n_tiles,
                                                      uint32_t *__restrict__ ranges,
                                                      uint32_t *__restrict__ ids) {
     __shared__ uint32_t s_keys[kTile];
@@ -1122,15 +1170,15 @@ __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict_
         const uint32_t b = blockIdx.x, nbs = s_P[b + 1] - s_P[b];
         uint32_t first = 0, end = 0;
         if (nbs) {
-            const int64_t h0 = (int64_t)kRadix * s_P[b];
-            first = hseg[h0 + (int64_t)tid * nbs];
-            end = tid < kRadix - 1 ? hseg[h0 + (int64_t)(tid + 1) * nbs] : s_S[b + 1];
+            const int64_t h0 = (int64_t)kRadix * s_P[b], hs = alone ? 1 : nbs;
+            first = hseg[h0 + tid * hs];
+            end = tid < kRadix - 1 ? hseg[h0 + (tid + 1) * hs] : s_S[b + 1];
             if (first == end) first = end = 0u;
         }
         ranges[2 * (int64_t)tile] = first;
         ranges[2 * (int64_t)tile + 1] = end;
     }
-    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x);
+    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x, alone);
     if (!sb.real) return;                      // uniform over the block
     const int cnt = (int)sb.cnt;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -1169,7 +1217,7 @@ __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict_
             s_wrun[q][tid] = r;
             r += c[q];
         }
-        s_goff[tid] = hseg[sb.h0 + (int64_t)tid * sb.nbs] - prefix;
+        s_goff[tid] = hseg[sb.h0 + (int64_t)tid * sb.hs] - prefix;
     }
     __syncthreads();
 #pragma unroll
@@ -1363,7 +1411,7 @@ hipError_t bin_finish_fused(const float *rec, const BinBufs &u, int64_t n, const
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_seg_scatter, dim3(L.seg_blocks), dim3(kBlk), 0, s,
                        (const uint32_t *)u.packed, (const uint32_t *)u.seg, nbk,
-                       (const uint32_t *)u.hseg, (const int64_t *)b.status, (uint32_t)L.n_tiles,
+                       (const uint32_t *)u.hseg, (const int64_t *)b.status, alone, (uint32_t)L.n_tiles,
                        b.ranges, b.ids);
     return hipGetLastError();
 }
