@@ -59,7 +59,9 @@ __global__ __launch_bounds__(kThreads) void k_affine(Groups<bz_affine_group> a) 
     int64_t i;
     const bz_affine_group &p = a.g[group_of(a, i)];
     if (i >= p.n) return;
-    p.dst[i] = (p.src[i] + p.add) * (i & 1 ? p.scale_odd : p.scale_even);
+    float x = p.src[i];
+    if (p.add != 0.f) x += p.add;               // a plain copy keeps the sign of zero
+    p.dst[i] = x * (i & 1 ? p.scale_odd : p.scale_even);
 }
 
 // Blocks of n_groups groups into a; false: too many for one grid.

@@ -80,13 +80,14 @@ def test_push_copies_the_bits():
         f.ctrl_n.mul_(1.37)
         f.ctrl_n.view(-1)[5] = float("nan")
         f.width.add_(0.123)
+        f.color.view(-1)[2] = -0.0
     version = f.rast.ctrl._version
     f.push()
     assert f.rast.ctrl._version > version
     want = (f.ctrl_n.detach() + 1.0) * f.half
     assert torch.equal(f.rast.ctrl.view(torch.int32), want.view(torch.int32).view(f.rast.ctrl.shape))
     assert torch.equal(f.rast.stroke_w, f.width.detach())
-    assert torch.equal(f.rast.color, f.color.detach())
+    assert torch.equal(f.rast.color.view(torch.int32), f.color.detach().view(torch.int32))
     assert torch.equal(f.rast.opacity, f.opacity.detach())
 
 
