@@ -564,11 +564,10 @@ class Rasterizer:
 
         The status words travel to pinned memory before the forward pass starts, and
         the host waits for them while it runs (blending skips overflowed lists); it
-        runs again after a growth.  A 1024x1024 initialiser frame: 106 -> 95 us
+        runs again after a growth.  A 1024x1024 frame of 8,192 strokes: 106 -> 95 us
         against waiting first, when the device idles until the host has woken."""
         torch = self.torch
-        self.sample()
-        self.bin()
+        self.sample_bin()
         if self._host_status is None:
             self._host_status = torch.empty(2, dtype=torch.int64, pin_memory=True)
             self._binned = torch.cuda.Event()

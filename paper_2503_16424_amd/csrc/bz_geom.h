@@ -176,17 +176,19 @@ struct Geom {
 // Geometry of Gaussian (r, k): Eq. sigma with the nearest-neighbour rule at
 // the last column / row, Eq. rotation one-sided at the row ends, unit tangent
 // (1, 0) when the chord has zero length.
-__device__ inline void gauss_geom(const CurveView &v, const double2 *XA, const double2 *XB, int r,
-                                  int k, double inv_rho2, double s0, Geom &g) {
+// at(r, k): sample point X_{r,k}.
+template <typename At>
+__device__ inline void gauss_geom_of(const CurveView &v, At at, int r, int k, double inv_rho2,
+                                     double s0, Geom &g) {
     int K = v.K;
     double t;
     column_param(k, K, v.S, g.seg, t);
     // The stencils use at most the point, its row neighbours and one row
     // neighbour: each is evaluated once (the same values as evaluating them
     // per use).
-    g.mu = sample_at(v, XA, XB, r, k);
-    const double2 Xl = k > 0 ? sample_at(v, XA, XB, r, k - 1) : g.mu;
-    const double2 Xr = k < K - 1 ? sample_at(v, XA, XB, r, k + 1) : g.mu;
+    g.mu = at(r, k);
+    const double2 Xl = k > 0 ? at(r, k - 1) : g.mu;
+    const double2 Xr = k < K - 1 ? at(r, k + 1) : g.mu;
     if (k < K - 1) { g.ka = k + 1; g.kb = k; } else { g.ka = K - 1; g.kb = K - 2; }
     const double2 A = k < K - 1 ? Xr : g.mu, B = k < K - 1 ? g.mu : Xl;   // X[r][ka], X[r][kb]
     g.d_along = make_double2(A.x - B.x, A.y - B.y);
@@ -194,7 +196,7 @@ __device__ inline void gauss_geom(const CurveView &v, const double2 *XA, const d
     if (v.kind == BZ_CLOSED) {
         int R1 = v.R + 1;
         if (r < R1) { g.ra = r + 1; g.rb = r; } else { g.ra = R1; g.rb = R1 - 1; }
-        const double2 Y = sample_at(v, XA, XB, r < R1 ? r + 1 : r - 1, k);
+        const double2 Y = at(r < R1 ? r + 1 : r - 1, k);
         const double2 P = r < R1 ? Y : g.mu, Q = r < R1 ? g.mu : Y;      // X[ra][k], X[rb][k]
         g.d_across = make_double2(P.x - Q.x, P.y - Q.y);
         g.sy2 = (g.d_across.x * g.d_across.x + g.d_across.y * g.d_across.y) * inv_rho2 + s0;
@@ -219,6 +221,25 @@ __device__ inline void gauss_geom(const CurveView &v, const double2 *XA, const d
         g.cs = 1.0;
         g.sn = 0.0;
     }
+}
+
+// From the boundary rows in LDS.
+__device__ inline void gauss_geom(const CurveView &v, const double2 *XA, const double2 *XB, int r,
+                                  int k, double inv_rho2, double s0, Geom &g) {
+    gauss_geom_of(v, [&](int rr, int kk) { return sample_at(v, XA, XB, rr, kk); }, r, k, inv_rho2,
+                  s0, g);
+}
+
+// From the control points, every sample evaluated where it is used.
+__device__ inline void gauss_geom_direct(const CurveView &v, int r, int k, double inv_rho2,
+                                         double s0, Geom &g) {
+    gauss_geom_of(v, [&](int rr, int kk) {
+        const double2 a = boundary_point(v, false, kk);
+        if (v.kind != BZ_CLOSED) return a;
+        const double t = (double)v.tau[rr];
+        const double2 b = boundary_point(v, true, kk);
+        return make_double2((1.0 - t) * a.x + t * b.x, (1.0 - t) * a.y + t * b.y);
+    }, r, k, inv_rho2, s0, g);
 }
 
 }  // namespace bz
