@@ -1126,6 +1126,19 @@ __global__ void k_zero(float *p, int64_t n) {
     for (; i < n; i += stride) p[i] = 0.f;
 }
 
+// Sum over the NT lanes of a curve: in all lanes for a whole wave, in the last of 16 or 32
+// otherwise.
+template <int NT>
+__device__ inline float lanes_sum(float v) {
+    if (NT >= kWave) return wave_sum(v);
+    v += dpp_f32<0x111, 0xF, true>(v);
+    v += dpp_f32<0x112, 0xF, true>(v);
+    v += dpp_f32<0x114, 0xF, true>(v);
+    v += dpp_f32<0x118, 0xF, true>(v);
+    if (NT == 32) v += dpp_f32<0x142, 0xA, false>(v);
+    return v;
+}
+
 // Stage 2: one workgroup per curve.  Per Gaussian (r, k) the gradients of
 // (mean, Q, o, colour) are chained to the sample points of its stencil:
 //   Q = R diag(a, b) R^T, a = 1/sx2, b = 1/sy2, (c, s) = v/|v|,
@@ -1144,29 +1157,41 @@ __global__ void k_zero(float *p, int64_t n) {
 // NT threads per curve.  Two launches split the curves by size: those of at
 // most kSmallCurve Gaussians (open strokes) run as one-wave workgroups with
 // LDS sized for them, the others with kCurveThreads threads; each launch
-// skips the other's curves.  lk and lg are the K and Gaussian capacities the
+// skips the other's curves.  Where no curve has more than 32 (16) Gaussians and the
+// chip is full, two (four) share a wave: 35,000 strokes of 16 to 32 samples 62 -> 50 us.  lk and lg are the K and Gaussian capacities the
 // dynamic LDS is laid out for.
 // Eight waves per SIMD (at most 64 VGPRs; 49 used): the stage waits on
-// latency, and at seven it ran 5% slower.
+// latency, and at seven it ran 5% slower.  Sharing curves hold theirs in 82 vector
+// registers; held to 64 they spill (73 us).
 //
 // kPacked: d_gauss holds nine floats per Gaussian, and the nine planes are
 // written to planes as they are read.
 template <int NT, bool kPacked>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_bwd_curves(bz_curves c, int lk, int lg, double inv_rho2,
+__global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_waves_per_eu(NT < kWave ? 5 : 8, 8))) void k_bwd_curves(bz_curves c, int lk, int lg, double inv_rho2,
                                                    double s0, const float *__restrict__ d_gauss,
                                                    float *__restrict__ planes,
                                                    int64_t ng, float *__restrict__ d_ctrl,
                                                    float *__restrict__ d_width,
                                                    float *__restrict__ d_color,
                                                    float *__restrict__ d_opacity) {
-    extern __shared__ double2 lds_xy[];
-    __shared__ float s_tau[256];
-    __shared__ float s_red[NT / 64][8];
-    __shared__ float s_cp[2][3 * kMaxSeg + 1][2];
-    const int p = blockIdx.x;
-    const bool small = c.gauss_off[p + 1] - c.gauss_off[p] <= kSmallCurve;
-    if (small != (NT == kWave)) return;   // the other launch's curve
-    const int lane = threadIdx.x;          // thread of the curve's workgroup
+    constexpr int kShare = NT < kWave ? kWave / NT : 1;    // curves per wave
+    extern __shared__ double2 lds_all[];
+    __shared__ float s_taus[kShare][kShare > 1 ? NT : 256];
+    __shared__ float s_red[kShare > 1 ? 1 : NT / 64][8];
+    __shared__ float s_cps[kShare][2][3 * kMaxSeg + 1][2];
+    const int sub = kShare > 1 ? threadIdx.x / NT : 0;
+    const int p = blockIdx.x * kShare + sub;
+    const int lane = kShare > 1 ? threadIdx.x % NT : threadIdx.x;   // thread of the curve
+    if (kShare > 1) {
+        if (p >= c.n_curves) return;
+    } else {
+        const bool small = c.gauss_off[p + 1] - c.gauss_off[p] <= kSmallCurve;
+        if (small != (NT == kWave)) return;   // the other launch's curve
+    }
+    double2 *const lds_xy = reinterpret_cast<double2 *>(
+        reinterpret_cast<char *>(lds_all) + sub * (stage2_terms_offset(lk) + 4 * 8 * lg));
+    float *const s_tau = s_taus[sub];
+    float (*const s_cp)[3 * kMaxSeg + 1][2] = s_cps[sub];
     CurveView v = load_curve_view(c, p);
     stage_tau(v, s_tau, lane, NT);
     // [K] column differences of the boundary samples: DA[k] = XA[k+1] - XA[k],
@@ -1335,21 +1360,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
         if (k >= K) { k -= K; ++r; }
     }
 
-    // per-curve sums: wave reduction, then across the workgroup's waves
-    wbar = wave_sum(wbar);
-    cb0 = wave_sum(cb0);
-    cb1 = wave_sum(cb1);
-    cb2 = wave_sum(cb2);
+    // per-curve sums: wave (or part of one) reduction, then across the workgroup's waves
+    wbar = lanes_sum<NT>(wbar);
+    cb0 = lanes_sum<NT>(cb0);
+    cb1 = lanes_sum<NT>(cb1);
+    cb2 = lanes_sum<NT>(cb2);
 #pragma unroll
-    for (int q = 0; q < kMaxSeg; ++q) ob[q] = wave_sum(ob[q]);
-    if ((lane & 63) == 0) {
+    for (int q = 0; q < kMaxSeg; ++q) ob[q] = lanes_sum<NT>(ob[q]);
+    if (kShare == 1 && (lane & 63) == 0) {
         float *sr = s_red[lane >> 6];
         sr[0] = wbar; sr[1] = cb0; sr[2] = cb1; sr[3] = cb2;
 #pragma unroll
         for (int q = 0; q < kMaxSeg; ++q) sr[4 + q] = ob[q];
     }
     __syncthreads();
-    if (lane == 0) {
+    if (lane == (kShare > 1 ? NT - 1 : 0)) {
         for (int wv = 1; wv < NT / 64; ++wv) {
             wbar += s_red[wv][0]; cb0 += s_red[wv][1]; cb1 += s_red[wv][2]; cb2 += s_red[wv][3];
 #pragma unroll
@@ -1632,6 +1657,11 @@ hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
     return hipGetLastError();
 }
 
+// Curves from which short ones share waves: four waves per SIMD without sharing.  2,048
+// curves of 32 samples and one segment 14.0 -> 12.0 us, but of 24 and three 11.7 ->
+// 12.9, where the longest chain counts, not the number of waves.
+constexpr int kShareCurves = 4096;
+
 template <bool kPacked>
 void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, float *planes,
                    const bz_grads &gr, hipStream_t s) {
@@ -1642,6 +1672,15 @@ void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, f
                            dim3(kCurveThreads), lds, s, c, c.max_k, c.max_gauss_per_curve, inv_rho2,
                            s0, d_gauss, planes, c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color,
                            gr.d_opacity);
+    }
+    if (c.max_gauss_per_curve <= 32 && c.n_curves >= kShareCurves) {
+        const int share = c.max_gauss_per_curve <= 16 ? 4 : 2;
+        const int64_t lds = share * stage2_lds_bytes(c.max_k, c.max_gauss_per_curve);
+        hipLaunchKernelGGL((share == 4 ? k_bwd_curves<16, kPacked> : k_bwd_curves<32, kPacked>),
+                           dim3((c.n_curves + share - 1) / share), dim3(kWave), lds, s, c, c.max_k,
+                           c.max_gauss_per_curve, inv_rho2, s0, d_gauss, planes, c.n_gauss,
+                           gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
+        return;
     }
     // a small curve has K <= its Gaussian count <= kSmallCurve
     const int lk = c.max_k < kSmallCurve ? c.max_k : kSmallCurve;
