@@ -97,16 +97,19 @@ __global__ void k_order_counts(bz_curves c, const uint32_t *vals, int32_t *order
     cnt[p] = curve_gauss(c, i);
 }
 
-// The whole order of up to kOrderMost curves in one workgroup: a bitonic sort in
-// LDS of (canvas, area key, curve) packed in 64 bits (all different, so ties end by
-// index as a stable sort leaves them), then the first Gaussian of each position by
-// a scan.  m: the power of two (at least 64) the list is filled up to, blockDim.x =
-// min(1024, max(64, m / 2)).  A wave's 64 pairs of a step of stride up to 64 lie in
-// 128 consecutive keys that no other wave touches: only longer strides need the
-// block's barrier.  Bound by the chain of steps (45 for 512 keys, 78 for 4096): 14 us
-// for 400 curves against 130 us for four radix passes of four launches each, the
-// counts and their scan.
+// The whole order of up to kOrderMost curves in one workgroup: (canvas, area key,
+// curve) packed in 64 bits (all different, so ties end by index as a stable sort leaves
+// them), ordered in LDS, then the first Gaussian of each position by a scan.  m: the
+// power of two (at least 64) the list is filled up to.
+// - Up to kRankMost curves a key's place is the number of smaller keys, counted by a
+//   thread per key (blockDim.x = m): every lane reads the same two keys at a time.
+// - More are sorted bitonically (blockDim.x = min(1024, m / 2)).  A wave's 64 pairs of
+//   a step of stride up to 64 lie in 128 consecutive keys that no other wave touches:
+//   only longer strides need the block's barrier.  Bound by the chain of steps (45 for
+//   512 keys, 78 for 4096): 14 us for 400 curves, where the ranks leave 8.6, against
+//   130 us for four radix passes of four launches each, the counts and their scan.
 constexpr int kOrderMost = 4096;
+constexpr int kRankMost = 512;
 
 __device__ inline void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -114,24 +117,8 @@ __device__ inline void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(1024) void k_order_small(bz_curves c, const bz_canvas *cv, int n_canvas,
-                                                      const float *area, int m, int32_t *order,
-                                                      int64_t *gauss_off) {
-    __shared__ uint64_t key[kOrderMost];
-    __shared__ uint64_t s_wave[16];
-    const int n = c.n_curves, t = threadIdx.x, nt = blockDim.x;
-    for (int i = t; i < m; i += nt) {
-        uint64_t k = ~0ull;                     // after every curve
-        if (i < n) {
-            const uint32_t canvas =
-                cv ? (uint32_t)batch_find(cv, n_canvas, (int64_t)i,
-                                          [](const bz_canvas &r) { return (int64_t)r.curve_off; })
-                   : 0u;
-            k = ((uint64_t)canvas << 48) | ((uint64_t)area_key(area[i]) << 16) | (uint64_t)i;
-        }
-        key[i] = k;
-    }
-    __syncthreads();
+// Ends with the block's barrier.
+__device__ inline void bitonic_sort(uint64_t *key, int m, int t, int nt) {
     bool wide = false;                          // the step before crossed waves
     for (int k = 2; k <= m; k <<= 1) {
         for (int d = k >> 1; d > 0; d >>= 1) {
@@ -149,6 +136,40 @@ __global__ __launch_bounds__(1024) void k_order_small(bz_curves c, const bz_canv
         }
     }
     __syncthreads();
+}
+
+__global__ __launch_bounds__(1024) void k_order_small(bz_curves c, const bz_canvas *cv, int n_canvas,
+                                                      const float *area, int m, int32_t *order,
+                                                      int64_t *gauss_off) {
+    __shared__ __align__(16) uint64_t key[kOrderMost];
+    __shared__ uint64_t s_wave[16];
+    const int n = c.n_curves, t = threadIdx.x, nt = blockDim.x;
+    for (int i = t; i < m; i += nt) {
+        uint64_t k = ~0ull;                     // after every curve
+        if (i < n) {
+            const uint32_t canvas =
+                cv ? (uint32_t)batch_find(cv, n_canvas, (int64_t)i,
+                                          [](const bz_canvas &r) { return (int64_t)r.curve_off; })
+                   : 0u;
+            k = ((uint64_t)canvas << 48) | ((uint64_t)area_key(area[i]) << 16) | (uint64_t)i;
+        }
+        key[i] = k;
+    }
+    __syncthreads();
+    if (m <= kRankMost) {
+        // a key's place is the number of smaller ones: a thread per key, two keys per
+        // LDS read, the same for all lanes
+        const uint64_t mine = key[t];
+        int rank = 0;
+        for (int i = 0; i < n; i += 2) {
+            const ulonglong2 two = *reinterpret_cast<const ulonglong2 *>(&key[i]);
+            rank += (two.x < mine) + (two.y < mine);
+        }
+        __syncthreads();
+        if (t < n) key[rank] = mine;
+        __syncthreads();
+    } else
+        bitonic_sort(key, m, t, nt);
     // per thread consecutive positions; the scan as in the binning
     const int per = (m + nt - 1) / nt, p0 = t * per;
     uint64_t sum = 0;
@@ -187,9 +208,12 @@ __global__ void k_zero1(float *p) {
     if (threadIdx.x == 0) p[0] = 0.f;
 }
 
-__global__ __launch_bounds__(256) void k_xing(bz_curves c, float weight, float *loss,
-                                              float *d_ctrl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// kAlone: one workgroup has every curve and stores the loss; otherwise each adds its
+// part to a loss that is zero already.
+template <int NT, bool kAlone>
+__global__ __launch_bounds__(NT) void k_xing(bz_curves c, float weight, float *loss,
+                                             float *d_ctrl) {
+    const int i = blockIdx.x * NT + threadIdx.x;
     double l = 0.0;
     if (i < c.n_curves && c.kind[i] == BZ_CLOSED) {
         const CurveView v = load_curve_by_id(c, i);
@@ -232,12 +256,18 @@ __global__ __launch_bounds__(256) void k_xing(bz_curves c, float weight, float *
         }
     }
     if (loss) {
-        __shared__ double part[4];
+        __shared__ double part[NT / 64];
         double s = wave_sum_d(l);
         if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
         __syncthreads();
-        if (threadIdx.x == 0)
-            atomicAdd(loss, (float)(weight * (part[0] + part[1] + part[2] + part[3])));
+        if (threadIdx.x == 0) {
+            double sum = 0.0;
+            for (int w = 0; w < NT / 64; ++w) sum += part[w];
+            if (kAlone)
+                loss[0] = (float)(weight * sum);
+            else
+                atomicAdd(loss, (float)(weight * sum));
+        }
     }
 }
 
@@ -291,7 +321,7 @@ hipError_t launch_area_order(const bz_curves &c, const bz_batch *batch, float *a
     if (n <= kOrderMost && (!batch || batch->n_canvas <= 65536)) {
         int m = 64;
         while (m < n) m *= 2;
-        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(m < 128 ? 64 : m > 2048 ? 1024 : m / 2), 0, s,
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(m <= kRankMost ? m : m > 2048 ? 1024 : m / 2), 0, s,
                            c, batch ? batch->canvas : nullptr, batch ? batch->n_canvas : 0,
                            (const float *)area, m, order, gauss_off);
         return hipGetLastError();
@@ -317,10 +347,15 @@ hipError_t launch_area_order(const bz_curves &c, const bz_batch *batch, float *a
 
 hipError_t launch_xing(const bz_curves &c, float weight, float *loss, float *d_ctrl,
                        hipStream_t s) {
+    // one workgroup, one launch: 9 -> 5 us for 400 curves
+    if (c.n_curves > 0 && c.n_curves <= 512) {
+        hipLaunchKernelGGL((k_xing<512, true>), dim3(1), dim3(512), 0, s, c, weight, loss, d_ctrl);
+        return hipGetLastError();
+    }
     if (loss) hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, s, loss);
     if (c.n_curves > 0)
-        hipLaunchKernelGGL(k_xing, dim3((unsigned)cdiv(c.n_curves, 256)), dim3(256), 0, s, c,
-                           weight, loss, d_ctrl);
+        hipLaunchKernelGGL((k_xing<256, false>), dim3((unsigned)cdiv(c.n_curves, 256)), dim3(256), 0,
+                           s, c, weight, loss, d_ctrl);
     return hipGetLastError();
 }
 
