@@ -353,6 +353,15 @@ bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const
                                 const bz_pixstate *state, bz_grads *grads, float *scratch,
                                 int64_t scratch_bytes, hipStream_t stream);
 
+/* One optimisation step: bz_sample_bin, bz_render_fwd_l2 and bz_render_bwd_scratch on
+ * the same arguments, their argument errors all found before the first launch, and the
+ * same results (up to the order of the float atomics); what the three clear is cleared
+ * in one launch where the sums are few. */
+bz_status bz_step(const bz_curves *c, const bz_opts *opts, bz_gaussians *g, bz_bins *b,
+                  float *image, bz_pixstate *state, const float *target, float scale,
+                  float *d_image, float *loss, bz_grads *grads, float *scratch,
+                  int64_t scratch_bytes, hipStream_t stream);
+
 /* Host: bytes of scratch bz_render_bwd_scratch needs for n_gauss Gaussians. */
 bz_status bz_bwd_scratch_size(int64_t n_gauss, int64_t *bytes);
 

@@ -91,7 +91,7 @@ EXPORTS = ("bz_layout_host", "bz_workspace_size", "bz_num_tiles", "bz_batch_layo
            "bz_curve_area", "bz_area_order_workspace", "bz_area_order", "bz_xing_loss",
            "bz_l2_grad", "bz_status_str", "bz_peak_run", "bz_peak_work",
            "bz_sample_bin_static", "bz_bwd_scratch_size", "bz_render_bwd_scratch",
-           "bz_adam_step", "bz_affine_copy")
+           "bz_adam_step", "bz_affine_copy", "bz_step")
 
 STATIC_SCRATCH_BYTES = 32 * 1024 * 1024   # BZ_STATIC_SCRATCH_BYTES of bz.h
 
@@ -161,6 +161,10 @@ def load_library(path: str = LIB_PATH):
     lib.bz_l2_grad.restype = C.c_int
     lib.bz_l2_grad.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_float, C.c_void_p,
                                C.c_void_p, C.c_void_p]
+    lib.bz_step.restype = C.c_int
+    lib.bz_step.argtypes = [P(Curves), P(Opts), P(Gaussians), P(Bins), C.c_void_p, P(PixState),
+                            C.c_void_p, C.c_float, C.c_void_p, C.c_void_p, P(Grads), C.c_void_p,
+                            C.c_int64, C.c_void_p]
     lib.bz_adam_step.restype = C.c_int
     lib.bz_adam_step.argtypes = [P(AdamGroup), C.c_int32, C.c_void_p]
     lib.bz_affine_copy.restype = C.c_int
@@ -581,10 +585,15 @@ class Rasterizer:
         return img
 
     def step(self, target):
-        """One fwd+bwd of the mean squared error against ``target`` (no sync)."""
-        self.sample_bin()
-        self.forward_l2(target)
-        self.backward()
+        """One fwd+bwd of the mean squared error against ``target`` (no sync):
+        sample_bin, forward_l2 and backward in one call."""
+        if self.draw_order == "area":
+            self.reorder()
+        _check("bz_step", self.lib.bz_step(
+            C.byref(self.curves), C.byref(self.opts), C.byref(self.gauss), C.byref(self.bins),
+            _ptr(self.image), self._state_arg(False), _ptr(target),
+            C.c_float(2.0 / (3 * self._hw)), _ptr(self.d_image), _ptr(self.loss),
+            C.byref(self.grads), _ptr(self.bwd_scratch), self.bwd_scratch.numel(), _stream()))
 
     # -- host views --------------------------------------------------------------
     def gaussians_host(self) -> dict:

@@ -319,9 +319,9 @@ bz_status bz_render_fwd(const bz_gaussians *g, const bz_bins *b, const bz_opts *
     return launched(launch_fwd(g->rec, *b, *o, image, state, nullptr, s));
 }
 
-bz_status bz_render_fwd_l2(const bz_gaussians *g, const bz_bins *b, const bz_opts *o, float *image,
-                           bz_pixstate *state, const float *target, float scale, float *d_image,
-                           float *loss, hipStream_t s) {
+static bz_status check_fwd_l2(const bz_gaussians *g, const bz_bins *b, const bz_opts *o,
+                              const float *image, const bz_pixstate *state, const float *target,
+                              float scale, const float *d_image) {
     bz_status st = check_opts(o);
     if (st != BZ_OK) return st;
     if (!g || g->n < 0 || (g->n > 0 && !g->rec)) return BZ_ERR_ARG;
@@ -329,7 +329,14 @@ bz_status bz_render_fwd_l2(const bz_gaussians *g, const bz_bins *b, const bz_opt
     if (!image || !target || !d_image || d_image == image) return BZ_ERR_ARG;
     if (!isfinite(scale)) return BZ_ERR_ARG;
     if ((st = check_state(state, o, b)) != BZ_OK) return st;
-    if ((st = check_persistent(b, o)) != BZ_OK) return st;
+    return check_persistent(b, o);
+}
+
+bz_status bz_render_fwd_l2(const bz_gaussians *g, const bz_bins *b, const bz_opts *o, float *image,
+                           bz_pixstate *state, const float *target, float scale, float *d_image,
+                           float *loss, hipStream_t s) {
+    bz_status st = check_fwd_l2(g, b, o, image, state, target, scale, d_image);
+    if (st != BZ_OK) return st;
     (void)hipGetLastError();
     const L2Out l2 = {target, d_image, loss, scale};
     return launched(launch_fwd(g->rec, *b, *o, image, state, &l2, s));
@@ -397,10 +404,10 @@ bz_status bz_bwd_scratch_size(int64_t n_gauss, int64_t *bytes) {
     return BZ_OK;
 }
 
-bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
-                                const bz_opts *o, const float *d_image, const bz_pixstate *state,
-                                bz_grads *gr, float *scratch, int64_t scratch_bytes,
-                                hipStream_t s) {
+static bz_status check_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
+                                   const bz_opts *o, const float *d_image,
+                                   const bz_pixstate *state, const bz_grads *gr,
+                                   const float *scratch, int64_t scratch_bytes) {
     bz_status st = check_opts(o);
     if (st != BZ_OK) return st;
     if ((st = check_curves(c)) != BZ_OK) return st;
@@ -411,9 +418,42 @@ bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const
     if (c->n_gauss > 0 && (!scratch || scratch == gr->d_gauss)) return BZ_ERR_ARG;
     int64_t need = 0;
     if ((st = bz_bwd_scratch_size(c->n_gauss, &need)) != BZ_OK) return st;
-    if (c->n_gauss > 0 && scratch_bytes < need) return BZ_ERR_CAPACITY;
+    return c->n_gauss > 0 && scratch_bytes < need ? BZ_ERR_CAPACITY : BZ_OK;
+}
+
+bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
+                                const bz_opts *o, const float *d_image, const bz_pixstate *state,
+                                bz_grads *gr, float *scratch, int64_t scratch_bytes,
+                                hipStream_t s) {
+    bz_status st = check_bwd_scratch(c, g, b, o, d_image, state, gr, scratch, scratch_bytes);
+    if (st != BZ_OK) return st;
     (void)hipGetLastError();
     st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s));
+    if (st != BZ_OK) return st;
+    return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
+}
+
+bz_status bz_step(const bz_curves *c, const bz_opts *o, bz_gaussians *g, bz_bins *b, float *image,
+                  bz_pixstate *state, const float *target, float scale, float *d_image,
+                  float *loss, bz_grads *gr, float *scratch, int64_t scratch_bytes,
+                  hipStream_t s) {
+    bz_status st = check_sample_bin(c, o, g, b);
+    if (st != BZ_OK) return st;
+    if ((st = check_bins(b, o, c->n_gauss, true)) != BZ_OK) return st;
+    bz_gaussians sampled = *g;
+    sampled.n = c->n_gauss;
+    if ((st = check_fwd_l2(&sampled, b, o, image, state, target, scale, d_image)) != BZ_OK)
+        return st;
+    if ((st = check_bwd_scratch(c, &sampled, b, o, d_image, state, gr, scratch, scratch_bytes)) !=
+        BZ_OK)
+        return st;
+    (void)hipGetLastError();
+    g->n = c->n_gauss;
+    const bool cleared = launch_step_clear(*c, *o, *b, loss, scratch, kGradPlanes * g->n, s);
+    const L2Out l2 = {target, d_image, loss, scale, cleared};
+    if ((st = launched(launch_sample_bin(*c, *o, g->rec, *b, s, cleared))) != BZ_OK) return st;
+    if ((st = launched(launch_fwd(g->rec, *b, *o, image, state, &l2, s))) != BZ_OK) return st;
+    st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s, cleared));
     if (st != BZ_OK) return st;
     return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
 }

@@ -710,6 +710,21 @@ __global__ void k_bucket_clear(int64_t *status, uint32_t *bucket, int64_t n) {
     if (i < 2) status[i] = 0;
 }
 
+// Start of a whole step: the same, the loss, and the sums of the backward's first
+// stage, in one launch instead of three (4.4, 3.8 and 4.8 us on a 128 x 128 frame).
+// Sums of more than kStepSums floats are cleared right before that stage, whose
+// atomics then find them in the memory-side cache.
+constexpr int64_t kStepSums = 9 * (int64_t(1) << 20);
+
+__global__ __launch_bounds__(256) void k_step_clear(int64_t *status, uint32_t *bucket, int64_t n,
+                                                    float *loss, float *sums, int64_t n_sums) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    if (i < 2) status[i] = 0;
+    if (i == 2 && loss) loss[0] = 0.f;
+    for (int64_t j = i; j < n; j += stride) bucket[j] = 0u;
+    for (; i < n_sums; i += stride) sums[i] = 0.f;
+}
 
 // Bucketed emission.  A bucket's pairs form one contiguous segment of the
 // packed array, emission block 0's first, then block 1's, ...: the scanned
@@ -1469,11 +1484,22 @@ hipError_t launch_bin(const float *rec_f, int64_t n, const bz_opts &o, const bz_
     return u.L.fused ? bin_finish_fused(rec_f, u, n, o, b, s) : bin_finish(rec_f, u, n, o, b, s);
 }
 
+bool launch_step_clear(const bz_curves &c, const bz_opts &o, const bz_bins &b, float *loss,
+                       float *sums, int64_t n_sums, hipStream_t s) {
+    const BinBufs u = bin_bufs(o, c.n_gauss, b);
+    if (!u.L.fused || c.n_gauss == 0 || n_sums > kStepSums) return false;
+    const int64_t nf = u.L.n_buckets * u.L.n_eblk;
+    const int64_t most = nf > n_sums ? nf : n_sums;
+    hipLaunchKernelGGL(k_step_clear, dim3((unsigned)cdiv(most, 1024)), dim3(256), 0, s, b.status,
+                       u.bucket, nf, loss, sums, n_sums);
+    return true;
+}
+
 hipError_t launch_sample_bin(const bz_curves &c, const bz_opts &o, float *rec, const bz_bins &b,
-                             hipStream_t s) {
+                             hipStream_t s, bool cleared) {
     const int64_t n = c.n_gauss;
     const BinBufs u = bin_bufs(o, n, b);
-    bin_prepare(u, b, n, s);
+    if (!cleared) bin_prepare(u, b, n, s);
     if (n == 0) return hipGetLastError();
     const BinCount bc = {u.counts, u.rects, b.status, 1.0f / o.tile_w, 1.0f / o.tile_h, o.tile_h,
                          support_two_p(o), u.bucket, u.L.n_eblk, (int)u.L.n_buckets,

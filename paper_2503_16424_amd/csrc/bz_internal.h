@@ -80,14 +80,19 @@ hipError_t launch_sample(const bz_curves &c, const bz_opts &o, float *rec, const
 hipError_t launch_bin(const float *rec, int64_t n_gauss, const bz_opts &o, const bz_bins &b,
                       hipStream_t s);
 // bz_sample_bin: binning with its counting pass done by the sampler.
+// Clears what a step's three parts clear, for launches that are then told so
+// (cleared); false: nothing done, they clear for themselves.
+bool launch_step_clear(const bz_curves &c, const bz_opts &o, const bz_bins &b, float *loss,
+                       float *sums, int64_t n_sums, hipStream_t s);
 hipError_t launch_sample_bin(const bz_curves &c, const bz_opts &o, float *rec,
-                             const bz_bins &b, hipStream_t s);
+                             const bz_bins &b, hipStream_t s, bool cleared = false);
 // The L2 loss gradient the forward can write with the image (loss may be null).
 struct L2Out {
     const float *target;
     float *d_image;
     float *loss;
     float scale;
+    bool cleared = false;     // the loss is zero already
 };
 // st == nullptr: the forward writes only the image; the backward recomputes
 // the blend state per tile.  l2 == nullptr: no loss gradient.  packed: d_gauss
@@ -96,7 +101,7 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
                       const bz_pixstate *st, const L2Out *l2, hipStream_t s);
 hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
                             const bz_opts &o, const float *d_image, const bz_pixstate *st,
-                            float *d_gauss, bool packed, hipStream_t s);
+                            float *d_gauss, bool packed, hipStream_t s, bool cleared = false);
 // planes non-null: d_gauss is packed (9 floats per Gaussian) and the planes are
 // written too.
 hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,

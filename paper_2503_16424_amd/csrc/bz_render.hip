@@ -1586,7 +1586,7 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
         a.l2_loss = l2->loss;
         a.l2_scale = l2->scale;
         a.l2_min_pairs = a.n_tiles > kLossTiles ? kLossPairs * (int64_t)a.n_tiles : 0;
-        if (l2->loss) hipLaunchKernelGGL(k_loss_zero, dim3(1), dim3(64), 0, s, l2->loss);
+        if (l2->loss && !l2->cleared) hipLaunchKernelGGL(k_loss_zero, dim3(1), dim3(64), 0, s, l2->loss);
     }
     if (st) {
         a.t_final = st->t_final;
@@ -1629,9 +1629,9 @@ int table_cap(size_t vis_bytes) {
 
 hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
                             const bz_opts &o, const float *d_image, const bz_pixstate *st,
-                            float *d_gauss, bool packed, hipStream_t s) {
+                            float *d_gauss, bool packed, hipStream_t s, bool cleared) {
     int64_t nz = (int64_t)kGradPlanes * n_gauss;
-    if (nz > 0) {
+    if (nz > 0 && !cleared) {
         int64_t blocks = cdiv(nz, 256);
         if (blocks > 16384) blocks = 16384;
         hipLaunchKernelGGL(k_zero, dim3(blocks), dim3(256), 0, s, d_gauss, nz);
