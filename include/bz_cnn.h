@@ -62,6 +62,16 @@ bz_status bz_conv_bwd_data(const bz_conv *cv, const float *dy, const uint16_t *w
 bz_status bz_conv_bwd_weight(const bz_conv *cv, const float *dy, const uint16_t *x,
                              float *dw, float *db, hipStream_t stream);
 
+/* bz_conv_bwd_weight without its clearing: adds to dw and db (a network clears the
+ * gradients of all its layers at once). */
+bz_status bz_conv_bwd_weight_add(const bz_conv *cv, const float *dy, const uint16_t *x,
+                                 float *dw, float *db, hipStream_t stream);
+
+/* BF16 pixels of c <= 8 channels (src, [n_pix][c]) to pixels of 8 with zeros behind
+ * (dst, [n_pix][8], 16-byte aligned), for convolutions that load 8 at a time. */
+bz_status bz_pad_channels(const uint16_t *src, int64_t n_pix, int32_t c, uint16_t *dst,
+                          hipStream_t stream);
+
 /* src FP32 -> dst BF16 (round to nearest even), n elements. */
 bz_status bz_f32_to_bf16(const float *src, uint16_t *dst, int64_t n, hipStream_t stream);
 

@@ -28,7 +28,7 @@ class ConvDesc(C.Structure):
 
 
 EXPORTS = ("bz_conv_shape", "bz_conv_fwd", "bz_conv_bwd_data", "bz_conv_bwd_weight",
-           "bz_f32_to_bf16", "bz_extract_patches")
+           "bz_f32_to_bf16", "bz_extract_patches", "bz_conv_bwd_weight_add", "bz_pad_channels")
 
 _ready = False
 
@@ -46,6 +46,10 @@ def lib():
         L.bz_conv_bwd_data.argtypes = [P(ConvDesc), V, V, V, V, V]
         L.bz_conv_bwd_weight.restype = C.c_int
         L.bz_conv_bwd_weight.argtypes = [P(ConvDesc), V, V, V, V, V]
+        L.bz_conv_bwd_weight_add.restype = C.c_int
+        L.bz_conv_bwd_weight_add.argtypes = [P(ConvDesc), V, V, V, V, V]
+        L.bz_pad_channels.restype = C.c_int
+        L.bz_pad_channels.argtypes = [V, C.c_int64, C.c_int32, V, V]
         L.bz_f32_to_bf16.restype = C.c_int
         L.bz_f32_to_bf16.argtypes = [V, V, C.c_int64, V]
         L.bz_extract_patches.restype = C.c_int
@@ -78,6 +82,24 @@ def conv_bwd_data(d, dy, w, dx, x_mask=None):
 def conv_bwd_weight(d, dy, x, dw, db=None):
     bz._check("bz_conv_bwd_weight", lib().bz_conv_bwd_weight(C.byref(d), _p(dy), _p(x), _p(dw),
                                                              _p(db), bz._stream()))
+
+
+def conv_bwd_weight_add(d, dy, x, dw, db=None):
+    """conv_bwd_weight into gradients that are added to."""
+    bz._check("bz_conv_bwd_weight_add", lib().bz_conv_bwd_weight_add(
+        C.byref(d), _p(dy), _p(x), _p(dw), _p(db), bz._stream()))
+
+
+def pad_channels(x, c):
+    """BF16 bits [..., x.shape[-1]] with zero channels up to c."""
+    torch = __import__("torch")
+    have = x.shape[-1]
+    if not (x.is_cuda and x.dtype == torch.int16 and x.is_contiguous() and c == 8 and have <= 8):
+        return torch.nn.functional.pad(x, (0, c - have))
+    out = torch.empty((*x.shape[:-1], c), dtype=x.dtype, device=x.device)
+    bz._check("bz_pad_channels", lib().bz_pad_channels(_p(x), x.numel() // max(have, 1), have,
+                                                       _p(out), bz._stream()))
+    return out
 
 
 def to_bf16(src, dst):
@@ -175,7 +197,7 @@ class CurveNet:
         torch = self.torch
         n = x.shape[0]
         ds, dsf = self._shapes(n), self._fwd_shapes(n)
-        x8 = torch.nn.functional.pad(x, (0, C0 - x.shape[-1]))      # BF16 zero bits
+        x8 = pad_channels(x, C0)
         acts = [x]
         for i in range(len(LAYERS)):
             d = dsf[i]
@@ -193,11 +215,13 @@ class CurveNet:
         torch = self.torch
         acts, ds = self._acts, self._ds
         d = dz.contiguous()
+        # every layer's gradients in one array, cleared in one launch
+        sizes = [t.numel() for t in self.tensors()]
+        grads = torch.zeros(sum(sizes), dtype=torch.float32, device=self.dev).split(sizes)
         for i in range(len(self.params) - 1, -1, -1):
             w, b = self.params[i]
-            dw = torch.empty_like(w)
-            db = torch.empty_like(b)
-            conv_bwd_weight(ds[i], d, acts[i], dw, db)
+            dw, db = grads[2 * i].view(w.shape), grads[2 * i + 1].view(b.shape)
+            conv_bwd_weight_add(ds[i], d, acts[i], dw, db)
             w.grad, b.grad = dw, db
             if i > 0:
                 dx = torch.empty(acts[i].shape, dtype=torch.float32, device=self.dev)
