@@ -72,6 +72,11 @@ bz_status bz_conv_bwd_weight_add(const bz_conv *cv, const float *dy, const uint1
 bz_status bz_pad_channels(const uint16_t *src, int64_t n_pix, int32_t c, uint16_t *dst,
                           hipStream_t stream);
 
+/* Raw outputs z [n_curves][per] to curve parameters: s = 1 / (1 + exp(-z)), of which the
+ * first `points` of a curve become s * scale - shift. */
+bz_status bz_decode(const float *z, int64_t n_curves, int32_t per, int32_t points, float scale,
+                    float shift, float *out, hipStream_t stream);
+
 /* src FP32 -> dst BF16 (round to nearest even), n elements. */
 bz_status bz_f32_to_bf16(const float *src, uint16_t *dst, int64_t n, hipStream_t stream);
 

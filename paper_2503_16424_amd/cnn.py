@@ -28,7 +28,8 @@ class ConvDesc(C.Structure):
 
 
 EXPORTS = ("bz_conv_shape", "bz_conv_fwd", "bz_conv_bwd_data", "bz_conv_bwd_weight",
-           "bz_f32_to_bf16", "bz_extract_patches", "bz_conv_bwd_weight_add", "bz_pad_channels")
+           "bz_f32_to_bf16", "bz_extract_patches", "bz_conv_bwd_weight_add",
+           "bz_pad_channels", "bz_decode")
 
 _ready = False
 
@@ -50,6 +51,8 @@ def lib():
         L.bz_conv_bwd_weight_add.argtypes = [P(ConvDesc), V, V, V, V, V]
         L.bz_pad_channels.restype = C.c_int
         L.bz_pad_channels.argtypes = [V, C.c_int64, C.c_int32, V, V]
+        L.bz_decode.restype = C.c_int
+        L.bz_decode.argtypes = [V, C.c_int64, C.c_int32, C.c_int32, C.c_float, C.c_float, V, V]
         L.bz_f32_to_bf16.restype = C.c_int
         L.bz_f32_to_bf16.argtypes = [V, V, C.c_int64, V]
         L.bz_extract_patches.restype = C.c_int
@@ -280,11 +283,27 @@ class TrainGraph:
         return self.z
 
 
+def _traced() -> bool:
+    """Whether torch follows the operations (transforms, forward-mode, tracing), so that a
+    library call would go unnoticed."""
+    torch = __import__("torch")
+    return (torch._C._functorch.maybe_current_level() is not None
+            or torch.autograd.forward_ad._current_level >= 0
+            or torch.jit.is_tracing() or torch.compiler.is_compiling())
+
+
 def decode(z, side=PATCH):
     """Raw outputs [n, 104] -> normalised curve parameters [n, 8, 13]:
     control points in patch sides (origin at the patch corner), then
     (width - 0.5) / 3.5, colour, opacity, each in [0, 1] for the last five."""
     torch = __import__("torch")
+    if (type(z) is torch.Tensor and z.is_cuda and z.dtype == torch.float32 and z.is_contiguous()
+            and z.numel() > 0 and z.numel() % OUT == 0
+            and not (torch.is_grad_enabled() and z.requires_grad) and not _traced()):
+        u = torch.empty((z.numel() // OUT, CURVES, PER_CURVE), dtype=z.dtype, device=z.device)
+        bz._check("bz_decode", lib().bz_decode(_p(z), z.numel() // PER_CURVE, PER_CURVE, 8,
+                                               1.0 + 2.0 * MARGIN, MARGIN, _p(u), bz._stream()))
+        return u
     s = torch.sigmoid(z.view(-1, CURVES, PER_CURVE))
     pts = s[..., :8] * (1.0 + 2.0 * MARGIN) - MARGIN
     return torch.cat([pts, s[..., 8:]], dim=-1)

@@ -1327,6 +1327,23 @@ __global__ __launch_bounds__(256) void k_pad8(const uint16_t *src, int64_t n_pix
     }
 }
 
+// Raw outputs to normalised curve parameters, one value per thread.  As five elementwise
+// passes and a concatenation 20 us for 1,024 patches, bound by launches.
+__global__ __launch_bounds__(256) void k_decode(const float *z, int64_t n, int per, int points,
+                                                float scale, float shift, float *out) {
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (; i < n; i += stride) {
+        const float s = 1.f / (1.f + expf(-z[i]));
+        float v = s;
+        if ((int)(i % per) < points) {
+            _Pragma("clang fp contract(off)") v = s * scale;
+            v = v - shift;
+        }
+        out[i] = v;
+    }
+}
+
 Shape shape_of(const bz_conv &c) {
     return Shape{c.n, c.h, c.w, c.c, c.k, c.r, c.stride, c.pad, c.ho, c.wo};
 }
@@ -1530,6 +1547,19 @@ bz_status bz_conv_bwd_weight_add(const bz_conv *cv, const float *dy, const uint1
     if (!dy || !x || !dw) return BZ_ERR_ARG;
     (void)hipGetLastError();
     return done(launch_conv_bwd_weight(*cv, dy, x, dw, db, true, s));
+}
+
+bz_status bz_decode(const float *z, int64_t n_curves, int32_t per, int32_t points, float scale,
+                    float shift, float *out, hipStream_t s) {
+    if (n_curves < 0 || per < 1 || points < 0 || points > per) return BZ_ERR_ARG;
+    if (n_curves == 0) return BZ_OK;
+    if (!z || !out) return BZ_ERR_ARG;
+    if (n_curves >= (int64_t(1) << 40) / per) return BZ_ERR_UNSUPPORTED;
+    (void)hipGetLastError();
+    const int64_t n = n_curves * per, b = cdiv(n, 256);
+    hipLaunchKernelGGL(k_decode, dim3((unsigned)(b < 8192 ? b : 8192)), dim3(256), 0, s, z, n, per,
+                       points, scale, shift, out);
+    return done(hipGetLastError());
 }
 
 bz_status bz_pad_channels(const uint16_t *src, int64_t n_pix, int32_t c, uint16_t *dst,

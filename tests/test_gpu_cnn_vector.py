@@ -133,3 +133,44 @@ def test_added_filter_gradients():
         cnn.conv_bwd_weight_add(d, dy, x, aw, ab)
         assert ((aw - 2.0) - dw).abs().max() <= 1e-5 * (dw.abs().max() + 2.0)
         assert ((ab + 3.0) - db).abs().max() <= 1e-5 * (db.abs().max() + 3.0)
+
+
+def _decode_reference(z):
+    import torch
+    from paper_2503_16424_amd import cnn
+    s = torch.sigmoid(z.view(-1, cnn.CURVES, cnn.PER_CURVE))
+    return torch.cat([s[..., :8] * (1.0 + 2.0 * cnn.MARGIN) - cnn.MARGIN, s[..., 8:]], dim=-1)
+
+
+@pytest.mark.parametrize("n", [1, 3, 1024])
+def test_decode_without_gradients(n):
+    """Sigmoid in FP32 and two roundings: 1e-6 absolute of values up to 1.25."""
+    import torch
+    from paper_2503_16424_amd import cnn
+    g = torch.Generator(device="cuda").manual_seed(n)
+    z = torch.randn((n, cnn.OUT), generator=g, device="cuda") * 4
+    z.view(-1)[3], z.view(-1)[11], z.view(-1)[5] = float("inf"), float("-inf"), float("nan")
+    got, want = cnn.decode(z), _decode_reference(z.double())
+    assert got.shape == want.shape and got.dtype == torch.float32
+    assert torch.equal(got.isnan(), want.isnan())
+    assert (got.double() - want).nan_to_num(0.0).abs().max() <= 1e-6
+
+
+def test_decode_where_torch_follows():
+    import torch
+    from paper_2503_16424_amd import cnn
+    z = torch.randn((4, cnn.OUT), device="cuda")
+    a = z.clone().requires_grad_()
+    cnn.decode(a).sum().backward()
+    b = z.clone().requires_grad_()
+    _decode_reference(b).sum().backward()
+    assert torch.equal(a.grad, b.grad)
+    t = torch.randn_like(z)
+    _, jvp = torch.func.jvp(cnn.decode, (z,), (t,))
+    _, ref = torch.func.jvp(_decode_reference, (z,), (t,))
+    assert torch.equal(jvp, ref)
+    with torch.autograd.forward_ad.dual_level():
+        out = cnn.decode(torch.autograd.forward_ad.make_dual(z, t))
+        assert torch.equal(torch.autograd.forward_ad.unpack_dual(out).tangent, ref)
+    assert torch.equal(torch.func.vmap(cnn.decode)(z.view(4, 1, -1)),
+                       torch.func.vmap(_decode_reference)(z.view(4, 1, -1)))
