@@ -11,7 +11,8 @@ from paper_2503_16424_amd import scenes
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("form", ["open", "mixed", "radix", "recompute", "batch", "area", "many"])
+@pytest.mark.parametrize("form", ["open", "mixed", "radix", "recompute", "batch", "area", "many",
+                                  "persistent", "unaligned"])
 def test_step_equals_its_parts(form):
     import torch
     from paper_2503_16424_amd import bz
@@ -21,16 +22,20 @@ def test_step_equals_its_parts(form):
         sc = scenes.uniform_open(3, 130, 70, 100, 16)
     elif form == "radix":
         opts = bz.RenderOptions(radix_bins=True)
+    elif form == "persistent":
+        opts = bz.RenderOptions(persistent=True)
     elif form == "recompute":
         kw = dict(blend_state="recompute")
     elif form == "batch":
         sc = scenes.batched(3, n_canvas=4, side=(40, 120), curves=(10, 60))
     elif form == "area":
         kw = dict(draw_order="area")
-    elif form == "many":                          # sums past the joint clear
+    elif form in ("many", "unaligned"):           # sums past the joint clear
         sc = scenes.uniform_open(4, 256, 256, 8200, 128)
     r = bz.Rasterizer(sc, opts, **kw)
     r.render()
+    if form == "unaligned":                       # the scratch needs 4-byte alignment only
+        r.bwd_scratch = torch.empty(r.bwd_scratch.numel() + 4, dtype=torch.uint8, device="cuda")[4:]
     n = 3 * r.n_pixels
     tgt = torch.rand(r.image.shape, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
     outs = ("image", "d_image", "ranges")
