@@ -449,11 +449,14 @@ bz_status bz_step(const bz_curves *c, const bz_opts *o, bz_gaussians *g, bz_bins
         return st;
     (void)hipGetLastError();
     g->n = c->n_gauss;
-    const bool cleared = launch_step_clear(*c, *o, *b, loss, scratch, kGradPlanes * g->n, s);
+    const int64_t sums = kGradPlanes * g->n;
+    const bool few = sums <= kStepSums;
+    const bool cleared = launch_step_clear(*c, *o, *b, loss, scratch, few ? sums : 0, s);
     const L2Out l2 = {target, d_image, loss, scale, cleared};
     if ((st = launched(launch_sample_bin(*c, *o, g->rec, *b, s, cleared))) != BZ_OK) return st;
     if ((st = launched(launch_fwd(g->rec, *b, *o, image, state, &l2, s))) != BZ_OK) return st;
-    st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s, cleared));
+    st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s,
+                                   cleared && few));
     if (st != BZ_OK) return st;
     return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
 }

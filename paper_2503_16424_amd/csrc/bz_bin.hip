@@ -712,10 +712,6 @@ __global__ void k_bucket_clear(int64_t *status, uint32_t *bucket, int64_t n) {
 
 // Start of a whole step: the same, the loss, and the sums of the backward's first
 // stage, in one launch instead of three (4.4, 3.8 and 4.8 us on a 128 x 128 frame).
-// Sums of more than kStepSums floats are cleared right before that stage, whose
-// atomics then find them in the memory-side cache.
-constexpr int64_t kStepSums = 9 * (int64_t(1) << 20);
-
 __global__ __launch_bounds__(256) void k_step_clear(int64_t *status, uint32_t *bucket, int64_t n,
                                                     float *loss, float *sums, int64_t n_sums) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1093,9 +1089,9 @@ __global__ __launch_bounds__(256) void k_seg_hist(const uint32_t *__restrict__ p
 // the counts in place: one workgroup per bucket, thread (part p, digit d) taking a
 // quarter of the blocks, 1 KiB rows at a time.  Counts laid out by block, not by digit:
 // there a radix block wrote its 256 counts into as many lines, shared with blocks on
-// other XCDs (7.2 M pairs: counts and scan 12.5 + 12.6 us that way, 9.1 + 9.8 this way).
-// Bound by latency: one read of up to 64 blocks' rows 4.0-4.7 us, the 10,000 blocks of a
-// 2048x2048 frame with 33.7 M pairs in 64 buckets 4.6 us (device-wide scan 10 + 9).
+// other XCDs (7.2 M pairs: counts and scan 12.5 + 12.6 us that way, 9.1 + 9.8 this way;
+// 33.7 M pairs, whose counts were 69 MB of partial lines for 10 MB, 66 + 14 and 55 +
+// 9.5).  Bound by latency: one read of up to 64 blocks' rows 4.0-4.7 us.
 __global__ __launch_bounds__(kOneThreads) void k_seg_scan(const uint32_t *__restrict__ seg, int nbk,
                                                           const int64_t *status, uint32_t *hseg) {
     constexpr int kParts = kOneThreads / kRadix;
@@ -1144,12 +1140,12 @@ __global__ __launch_bounds__(kOneThreads) void k_seg_scan(const uint32_t *__rest
 }
 
 // Whether each bucket's counts are scanned by one workgroup, which takes two rounds of
-// about 1 us for every 64 of its radix blocks after the first 64: up to 128 blocks per
+// about 1 us for every 64 of its radix blocks after the first 64: up to 256 blocks per
 // bucket on average (a batch whose canvases fill some buckets far more than others
-// 9.8 us against 11), and up to 512 in all, where the longest bucket cannot take
-// more than 16.
+// 9.8 us against 11; 33.7 M pairs in 64 buckets 9.5 against 14), and up to 512 in all,
+// where the longest bucket cannot take more than 16 rounds.
 inline bool seg_alone(const BinLayout &L) {
-    return L.seg_blocks <= 512 || L.seg_blocks <= 128 * L.n_buckets;
+    return L.seg_blocks <= 512 || L.seg_blocks <= 256 * L.n_buckets;
 }
 
 // The in-bucket pass's scatter: ranks as in k_radix_scatter (digit = key
@@ -1487,7 +1483,7 @@ hipError_t launch_bin(const float *rec_f, int64_t n, const bz_opts &o, const bz_
 bool launch_step_clear(const bz_curves &c, const bz_opts &o, const bz_bins &b, float *loss,
                        float *sums, int64_t n_sums, hipStream_t s) {
     const BinBufs u = bin_bufs(o, c.n_gauss, b);
-    if (!u.L.fused || c.n_gauss == 0 || n_sums > kStepSums) return false;
+    if (!u.L.fused || c.n_gauss == 0) return false;
     const int64_t nf = u.L.n_buckets * u.L.n_eblk;
     const int64_t most = nf > n_sums ? nf : n_sums;
     hipLaunchKernelGGL(k_step_clear, dim3((unsigned)cdiv(most, 1024)), dim3(256), 0, s, b.status,

@@ -80,8 +80,12 @@ hipError_t launch_sample(const bz_curves &c, const bz_opts &o, float *rec, const
 hipError_t launch_bin(const float *rec, int64_t n_gauss, const bz_opts &o, const bz_bins &b,
                       hipStream_t s);
 // bz_sample_bin: binning with its counting pass done by the sampler.
-// Clears what a step's three parts clear, for launches that are then told so
-// (cleared); false: nothing done, they clear for themselves.
+// Clears what a step's sampling, binning and loss start from, and n_sums floats of sums,
+// for launches that are then told so (cleared); false: nothing done, they clear for
+// themselves.
+// Sums of more than kStepSums floats are cleared right before the backward, whose
+// atomics then find them in the memory-side cache.
+constexpr int64_t kStepSums = 9 * (int64_t(1) << 20);
 bool launch_step_clear(const bz_curves &c, const bz_opts &o, const bz_bins &b, float *loss,
                        float *sums, int64_t n_sums, hipStream_t s);
 hipError_t launch_sample_bin(const bz_curves &c, const bz_opts &o, float *rec,

@@ -2,7 +2,7 @@
 
 Draw order: up to 4096 curves are sorted in one workgroup, more by radix passes;
 both must give numpy's stable order of the float keys (ties by index, NaN last).
-Tile lists: up to 512 radix blocks (from the pair buffer's size), or 128 per bucket,
+Tile lists: up to 512 radix blocks (from the pair buffer's size), or 256 per bucket,
 each bucket's digit counts are scanned by one workgroup, above that by the
 device-wide scan; the lists of a frame do not depend on the buffer's size, and an overflow leaves every
 range empty.  All whole numbers: compared exactly.
@@ -68,7 +68,7 @@ def test_lists_do_not_depend_on_the_buffer(tile):
     n_tiles = -(-500 // tile[0]) * -(-300 // tile[1])
     buckets = -(-n_tiles // 256)
     lists = []
-    most = max(512, 128 * buckets)
+    most = max(512, 256 * buckets)
     for blocks in (most, most + 1):
         cap = (blocks - buckets) * KEY_BLOCK
         r._alloc_pairs(cap)
