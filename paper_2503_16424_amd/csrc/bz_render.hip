@@ -629,9 +629,21 @@ constexpr int kSums = 10;     // sums over pixels of one Gaussian
 //   dL/dcolour = alpha T g.
 // Sums 0-9 are f G (1, dx, dy, dx^2, dx dy, dy^2), alpha T g (3) and f;
 // planes_of turns them into the planes with the record's shape.
-__device__ inline void planes_of(const TileArgs &a, uint32_t id, const float (&S)[kSums],
+//
+// In the packed form the three of the conic are kept in the Gaussian's principal frame
+// (t the tangent, n across): abar = -o' sum(f G t^2) / 2, bbar = -o' sum(f G n^2) / 2 and
+// D = -o' sum(f G t n), which are what stage 2 needs.  In x and y the moments along a
+// stroke, (sigma_x / sigma_y)^2 times those across it, would round the latter away in
+// every addition to memory, and a width's gradient is made of them alone: its error
+// against FP64 on the 2048x2048 frame 2e-5 that way, 1.5e-6 this way (the width of a
+// table's sums is double, so turning them costs the stage 1.2%, and stage 2 gets 6%
+// back).
+__device__ inline void planes_of(const TileArgs &a, uint32_t id, const double (&D)[kSums],
                                  float (&out)[kGradPlanes]) {
     const float4 q = a.rec[3 * (int64_t)id + 1];
+    float S[kSums];
+#pragma unroll
+    for (int v = 0; v < kSums; ++v) S[v] = (float)D[v];
     const float ex = kHalfLog2eSqrt * q.x, ey = kHalfLog2eSqrt * q.y;
     const float fx = q.z * ex, fy = q.z * ey;
     const float op = q.w * a.inv_1mg;
@@ -639,9 +651,17 @@ __device__ inline void planes_of(const TileArgs &a, uint32_t id, const float (&S
     const float k2 = 1.38629436112f * op;        // 2 ln 2 o'
     out[0] = k2 * fmaf(A, S[1], B * S[2]);
     out[1] = k2 * fmaf(B, S[1], C * S[2]);
-    out[2] = -0.5f * op * S[3];
-    out[3] = -op * S[4];
-    out[4] = -0.5f * op * S[5];
+    if (a.packed) {
+        const float inv = __frsqrt_rn(fmaf(q.x, q.x, q.y * q.y));
+        const double c = (double)(q.x * inv), s = (double)(q.y * inv), cs = c * s;
+        out[2] = -0.5f * op * (float)(c * c * D[3] + 2.0 * cs * D[4] + s * s * D[5]);
+        out[3] = -op * (float)(cs * (D[5] - D[3]) + (c * c - s * s) * D[4]);
+        out[4] = -0.5f * op * (float)(s * s * D[3] - 2.0 * cs * D[4] + c * c * D[5]);
+    } else {
+        out[2] = -0.5f * op * S[3];
+        out[3] = -op * S[4];
+        out[4] = -0.5f * op * S[5];
+    }
     out[5] = fmaf(-a.g_min, S[9], S[0]) * a.inv_1mg;
     out[6] = S[6];
     out[7] = S[7];
@@ -1058,9 +1078,10 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
                 if (q == 0) {                        // the slot's own column, in place
                     uint32_t id = kNoGauss;
                     if (live && p >= (uint32_t)tab_cap) {
-                        float S[kSums], o[kGradPlanes];
+                        double S[kSums];
+                        float o[kGradPlanes];
 #pragma unroll
-                        for (int v = 0; v < kSums; ++v) S[v] = wl.rec[v][s];
+                        for (int v = 0; v < kSums; ++v) S[v] = (double)wl.rec[v][s];
                         id = a.ids[start + p];
                         planes_of(a, id, S, o);
 #pragma unroll
@@ -1084,12 +1105,13 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
     uint32_t *fid = reinterpret_cast<uint32_t *>(wl.rec[9]);
     for (int p0 = 64 * w; p0 < tab_n; p0 += 64 * nwaves) {
         const int p = p0 + lane;
-        float S[kSums], o[kGradPlanes];
+        double S[kSums];
+        float o[kGradPlanes];
         bool any = false;
 #pragma unroll
         for (int v = 0; v < kSums; ++v) {
-            S[v] = p < tab_n ? (float)table[v * tab_p + p] : 0.f;
-            any |= S[v] != 0.f;
+            S[v] = p < tab_n ? table[v * tab_p + p] : 0.0;
+            any |= S[v] != 0.0;
         }
         uint32_t id = kNoGauss;
         if (any) {
@@ -1256,10 +1278,6 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
 #pragma unroll
         for (int q = 0; q < kGradPlanes; ++q)
             dg[q] = d_gauss[kPacked ? kGradPlanes * (v.g0 + idx) + q : q * ng + v.g0 + idx];
-        if (kPacked) {
-#pragma unroll
-            for (int q = 0; q < kGradPlanes; ++q) planes[q * ng + v.g0 + idx] = dg[q];
-        }
         // stencil (Eq. sigma with nearest-neighbour ends, Eq. rotation).  Row
         // r's samples are (1 - tau_r) XA + tau_r XB, so its differences along
         // the row are the same blend of DA and DB, and across rows
@@ -1298,11 +1316,23 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
         const float inv_nv = nv2 > 0.f ? __frsqrt_rn(nv2) : 0.f;
         const float cs = nv2 > 0.f ? vx * inv_nv : 1.f, sn = nv2 > 0.f ? vy * inv_nv : 0.f;
         const float ia = __builtin_amdgcn_rcpf(sx2), ib = __builtin_amdgcn_rcpf(sy2);
-        const float qxx = dg[2], qxy = dg[3], qyy = dg[4];
-        const float abar = qxx * cs * cs + qxy * cs * sn + qyy * sn * sn;
-        const float bbar = qxx * sn * sn - qxy * cs * sn + qyy * cs * cs;
-        const float cbar_t = qxx * 2.f * cs * ia + qxy * sn * (ia - ib) + qyy * 2.f * cs * ib;
-        const float sbar_t = qxx * 2.f * sn * ib + qxy * cs * (ia - ib) + qyy * 2.f * sn * ia;
+        // the conic's gradient in the principal frame: along, across and mixed
+        float abar, bbar, mixed;
+        if (kPacked) {
+            abar = dg[2];
+            mixed = dg[3];
+            bbar = dg[4];
+            dg[2] = cs * cs * abar - cs * sn * mixed + sn * sn * bbar;
+            dg[3] = 2.f * cs * sn * (abar - bbar) + (cs * cs - sn * sn) * mixed;
+            dg[4] = sn * sn * abar + cs * sn * mixed + cs * cs * bbar;
+#pragma unroll
+            for (int q = 0; q < kGradPlanes; ++q) planes[q * ng + v.g0 + idx] = dg[q];
+        } else {
+            const float qxx = dg[2], qxy = dg[3], qyy = dg[4];
+            abar = qxx * cs * cs + qxy * cs * sn + qyy * sn * sn;
+            bbar = qxx * sn * sn - qxy * cs * sn + qyy * cs * cs;
+            mixed = 2.f * cs * sn * (qyy - qxx) + (cs * cs - sn * sn) * qxy;
+        }
         const float f = 2.f * (-abar * ia * ia) * rho2f;
         const float sy2bar = -bbar * ib * ib;
         Tm[idx] = make_float2(dg[0], dg[1]);
@@ -1314,8 +1344,9 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             wbar += 2.f * v.width * sy2bar;
         }
         if (nv2 > 0.f) {
-            const float hd = cs * cbar_t + sn * sbar_t;
-            Tv[idx] = make_float2((cbar_t - cs * hd) * inv_nv, (sbar_t - sn * hd) * inv_nv);
+            // the tangent's gradient across itself: turning it mixes the two scales
+            const float h = (ia - ib) * mixed * inv_nv;
+            Tv[idx] = make_float2(-sn * h, cs * h);
         } else {
             Tv[idx] = make_float2(0.f, 0.f);
         }

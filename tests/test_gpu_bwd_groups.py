@@ -97,3 +97,33 @@ def test_nan_gradient_stays_in_its_tile():
     near[ids[ranges[0, 0]: ranges[0, 1]]] = True
     assert np.isnan(g[near]).any()
     assert np.isfinite(g[~near]).all()
+
+
+def test_width_gradients_of_long_strokes():
+    """Diagonal strokes much longer than wide: the moments along them are hundreds of
+    times those across, of which the width's gradient is made.  The step's gradients
+    against the stage-by-stage form with its planes in x and y: control points 1e-4, and
+    the widths no further off FP64 than that form's (1e-4 at most)."""
+    import torch
+
+    import oracle
+    from paper_2503_16424_amd import bz, scenes
+    from tests.helpers import rel_l2
+    sc = scenes.uniform_open(31, 256, 256, 24, 12)
+    r = bz.Rasterizer(sc)
+    r.render()
+    o0 = oracle.forward_backward(sc)
+    tgt = scenes.target_noise(3, sc.width, sc.height).astype(np.float64)
+    d = 2.0 * (o0["image"] - tgt) / o0["image"].size
+    o = oracle.forward_backward(sc, d)
+    dt = torch.as_tensor(d.astype(np.float32), device="cuda")
+    r.backward(dt)
+    got = {k: getattr(r, k).clone() for k in ("d_ctrl", "d_width")}
+    planes = r.d_gauss.clone()
+    r.backward_gauss(dt)
+    assert rel_l2(planes.cpu().numpy(), r.d_gauss.double().cpu().numpy()) <= 1e-5
+    r.backward_curves()
+    for k in got:
+        assert rel_l2(got[k].cpu().numpy(), o[k]) <= max(
+            1e-4, 1.5 * rel_l2(getattr(r, k).cpu().numpy(), o[k])), k
+    assert rel_l2(got["d_width"].cpu().numpy(), o["d_width"]) <= 1e-4
