@@ -342,7 +342,7 @@ def bench_curvenet(a):
            "config": {"workload": "curvenet-32x32-patches", "batch": a.batch,
                       "launch": "one HIP graph replay per step"},
            "ms_per_step_eager": step_ms_eager,
-           "roofline": {"kernel": f"k_igemm layer {dom['layer']} {dom['pass']}", "bound": "mfma",
+           "roofline": {"kernel": f"convolution layer {dom['layer']} {dom['pass']}", "bound": "mfma",
                         "achieved": dom["tflops"], "peak": PEAK_BF16_MFMA_TFLOPS,
                         "unit": "TFLOP/s", "frac": dom["tflops"] / PEAK_BF16_MFMA_TFLOPS,
                         "traffic": None},

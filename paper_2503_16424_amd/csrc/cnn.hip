@@ -12,6 +12,10 @@
 //   filter grad  m = out channel,  n = (dy, dx, in channel), k = output pixel
 //                A = output gradients, B = shifted input pixels
 //
+// Layers whose channel counts are multiples of 8 (every layer of the proposal network
+// but its first filter gradient) take the vector kernels, k_conv_rows and k_wgrad, the
+// others k_igemm:
+//
 // A workgroup (4 waves) computes a 64 x 64 tile of C in steps of 32 along k:
 // the 256 threads gather the A and B slices (8 consecutive k per thread) into
 // LDS with k contiguous, then each wave runs 2 x 2 v_mfma_f32_16x16x32_bf16 on
