@@ -1,7 +1,8 @@
 // bz_render.hip -- per-tile blending (Sec. 3.4) and its reverse pass.
 //
 // Work decomposition (forward and backward stage 1): one workgroup per tile,
-// one wave per 8x8 pixel quad of the tile, one pixel per lane.  Waves are
+// one wave per 8x8 pixel quad of the tile; in the forward one pixel per lane, in
+// the backward one list entry and a quarter of the pixels (BwdWave).  Waves are
 // independent: each walks its tile's list in batches of 64 entries; lane j
 // loads entry j's record, tests the entry's truncated support against the
 // quad (exact minimum of the quadratic form over the quad's pixel centres),
@@ -23,8 +24,8 @@
 // each pixel (k_fwd_l2), which spares the step a pass over the image.
 //
 // Stage 2 of the backward pass is per curve (one workgroup per curve: 64
-// threads for curves of at most 64 Gaussians, 256 for larger ones; no
-// atomics): it chains the per-Gaussian gradients through the sampling of
+// threads for curves of at most 64 Gaussians, 256 for larger ones, part of a
+// wave for short curves in large sets; no atomics): it chains the per-Gaussian gradients through the sampling of
 // Sec. 3.3.
 #include <cstddef>
 
