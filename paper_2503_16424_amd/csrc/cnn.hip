@@ -27,6 +27,7 @@
 // atomics.
 #include "bz_internal.h"
 #include "../../include/bz_cnn.h"
+#include "cnn_rows.h"
 
 namespace bz {
 
@@ -64,10 +65,6 @@ __device__ inline uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-struct Shape {
-    int n, h, w, c, k, r, s, p, ho, wo;
-};
-
 // Input pixel read by output pixel m through filter tap `tap`, or -1 (padding).
 __device__ inline int in_pixel(const Shape &S, int m, int tap) {
     const int hw = (int)S.ho * S.wo;
@@ -94,26 +91,6 @@ __device__ inline int out_pixel(const Shape &S, int m, int tap) {
     return (b * S.ho + oy) * S.wo + ox;
 }
 
-enum Mode { kFwd = 0, kBwdData = 1, kBwdWeight = 2 };
-
-struct GemmArgs {
-    Shape S;
-    int M, N, K;          // GEMM sizes
-    const uint16_t *x;        // input activations (bf16)
-    const uint16_t *w;        // filters (bf16)
-    const float *dy;          // output gradients (f32)
-    const float *bias;
-    const uint16_t *mask;     // bwd data: zero where the layer input is <= 0
-    int relu;
-    float *out_f;             // fwd y, bwd-data dx, bwd-weight dw
-    uint16_t *out_b;          // fwd y in bf16
-    int k_chunk;          // bwd weight: k range per workgroup
-    // bwd data, one parity class: rows are the input pixels (iy, ix) with
-    // iy = cy, ix = cx (mod stride), hq x wq of them per image; only taps
-    // ky = ky0, kx = kx0 (mod stride) reach them, nkx of them along x
-    int cy, cx, hq, wq, ky0, kx0, nkx;
-};
-
 // Input pixel of class row m (input gradient).
 __device__ inline int cls_pixel(const GemmArgs &g, int m) {
     if (g.S.s == 1) return m;                   // one class: every pixel
@@ -122,24 +99,6 @@ __device__ inline int cls_pixel(const GemmArgs &g, int m) {
     const int rem = (int)(m - b * hw);
     const int qy = rem / g.wq, qx = rem - (rem / g.wq) * g.wq;
     return (b * g.S.h + qy * g.S.s + g.cy) * g.S.w + qx * g.S.s + g.cx;
-}
-
-// Input gradient: the parity class of workgroup row z (cy = z / stride,
-// cx = z mod stride), its GEMM rows M and its k extent K.
-__device__ inline void set_class(GemmArgs &g, int z) {
-    const Shape &S = g.S;
-    const int st = S.s;
-    g.cy = z / st;
-    g.cx = z - (z / st) * st;
-    g.hq = g.cy < S.h ? (S.h - g.cy + st - 1) / st : 0;
-    g.wq = g.cx < S.w ? (S.w - g.cx + st - 1) / st : 0;
-    g.ky0 = (g.cy + S.p) % st;
-    g.kx0 = (g.cx + S.p) % st;
-    const int nky = g.ky0 < S.r ? (S.r - g.ky0 + st - 1) / st : 0;
-    const int nkx = g.kx0 < S.r ? (S.r - g.kx0 + st - 1) / st : 0;
-    g.nkx = nkx > 0 ? nkx : 1;                  // no taps: K = 0, the class gets zeros
-    g.M = (int)S.n * g.hq * g.wq;
-    g.K = (int)nky * nkx * S.k;
 }
 
 // Filter tap of the class's j-th (ky, kx) pair (input gradient).
@@ -465,38 +424,6 @@ __global__ __launch_bounds__(256) void k_igemm(GemmArgs args) {
 // -> 20, 22 -> 17, 78 -> 37 us, the 1 x 1 head 18 -> 12.  k steps in flight: 4
 // (forward) and 2 (the FP32 side); half as many cost the second layer's input
 // gradient 14%, twice as many the last layers' 15%.
-struct ConvTab {
-    int off;              // elements from the pixel's base to the slice
-    int16_t dy, dx;       // rows and columns from it (bounds test)
-};
-
-// A parity class (forward: the only one): its steps of 32 k and where they start.
-struct ConvClass {
-    int first, steps, cy, cx;
-};
-
-// The slice at class k `k` of g's current class, relative to the pixel's base.
-template <int MODE>
-__device__ inline ConvTab conv_tab(const GemmArgs &g, int k) {
-    const Shape &S = g.S;
-    ConvTab e;
-    const int sc = MODE == kFwd ? S.c : S.k;
-    const int j = k / sc, ch = k - j * sc;
-    if (MODE == kFwd) {
-        const int ky = j / S.r, kx = j - ky * S.r;
-        e.dy = (int16_t)ky;
-        e.dx = (int16_t)kx;
-        e.off = (ky * S.w + kx) * S.c + ch;
-    } else {
-        const int y = j / g.nkx, x = j - y * g.nkx;
-        const int dy = (g.cy + S.p - g.ky0) / S.s - y, dx = (g.cx + S.p - g.kx0) / S.s - x;
-        e.dy = (int16_t)dy;
-        e.dx = (int16_t)dx;
-        e.off = (dy * S.wo + dx) * S.k + ch;
-    }
-    if (k >= g.K) e.dy = 0x4000;                // no such slice: out of every bound
-    return e;
-}
 
 // Wave-level LDS ordering.
 __device__ inline void wave_fence() {
@@ -507,62 +434,10 @@ __device__ inline void wave_fence() {
 
 // LDS of a block: the filters of its columns, lane by lane; the slice table; the
 // classes; an output tile of 16 pixels per wave.
-__host__ __device__ inline int conv_steps(int K) { return (K + 31) / 32; }
 __host__ __device__ inline int conv_pitch(int nb, int out_bytes) { return 16 * nb * out_bytes + 16; }
 inline size_t conv_rows_lds(int64_t steps, int classes, int nb, int out_bytes, int waves) {
     return (size_t)steps * (nb * 1024 + 4 * sizeof(ConvTab)) + classes * sizeof(ConvClass) +
            (size_t)waves * 16 * conv_pitch(nb, out_bytes);
-}
-
-// Division of 0 <= m < 2^31 by d >= 1 without a divide per tile (Granlund and
-// Montgomery 1994): with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d) < 2^32,
-// m / d = (m * mul) >> (31 + s).
-struct Divisor {
-    uint32_t d, mul;
-    int sh;
-};
-
-__device__ inline Divisor divisor(int d) {
-    const int s = d > 1 ? 32 - __builtin_clz(d - 1) : 1;
-    return Divisor{(uint32_t)d, (uint32_t)(((1ull << (31 + s)) + d - 1) / (unsigned)d), s - 1};
-}
-
-__device__ inline int divide(int m, const Divisor &v) {
-    return v.d == 1 ? m : (int)(__umulhi((uint32_t)m, v.mul) >> v.sh);
-}
-
-// One row tile as a wave reads it: this lane's output pixel, or its block of
-// stride x stride input pixels, one of each class (input gradient).
-struct ConvRow {
-    int base, y0, x0, b;
-};
-
-template <int MODE>
-__device__ inline ConvRow conv_row(const GemmArgs &g, const Divisor &image, const Divisor &line,
-                                   int tile, int j) {
-    const Shape &S = g.S;
-    ConvRow r;
-    const int m = tile * 16 + j;
-    r.b = divide(m, image);
-    const int rem = m - r.b * (int)image.d;
-    const int ry = divide(rem, line), rx = rem - ry * (int)line.d;
-    r.y0 = MODE == kFwd ? ry * S.s - S.p : ry;
-    r.x0 = MODE == kFwd ? rx * S.s - S.p : rx;
-    r.base = MODE == kFwd ? ((r.b * S.h + r.y0) * S.w + r.x0) * S.c
-                          : ((r.b * S.ho + ry) * S.wo + rx) * S.k;
-    if (r.b >= S.n) r.y0 = -0x4000;             // no such row: out of every bound
-    return r;
-}
-
-// The pixel that the lane's sums belong to, or -1.
-template <int MODE>
-__device__ inline int conv_out(const GemmArgs &g, const ConvRow &r, int tile, int j,
-                               const ConvClass &cls) {
-    const Shape &S = g.S;
-    if (r.b >= S.n) return -1;
-    if (MODE == kFwd) return tile * 16 + j;
-    const int iy = r.y0 * S.s + cls.cy, ix = r.x0 * S.s + cls.cx;
-    return iy < S.h && ix < S.w ? (r.b * S.h + iy) * S.w + ix : -1;
 }
 
 template <int MODE, int NB>
@@ -621,11 +496,8 @@ __global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_step
         first += steps;
     }
     __syncthreads();                            // the block's only barrier
-    const Divisor image = divisor(MODE == kFwd ? S.ho * S.wo
-                                               : ((S.h + S.s - 1) / S.s) * ((S.w + S.s - 1) / S.s));
-    const Divisor line = divisor(MODE == kFwd ? S.wo : (S.w + S.s - 1) / S.s);
-    const int tiles = (int)(((int64_t)S.n * image.d + 15) / 16);
-    const int SH = MODE == kFwd ? S.h : S.ho, SW = MODE == kFwd ? S.w : S.wo;
+    const Divisor image = conv_image<MODE>(S), line = conv_line<MODE>(S);
+    const int tiles = conv_tiles(S, image);
     const int nwaves = (nt >> 6) * (int)gridDim.x;
     // workgroup b runs on XCD b % 8: neighbouring row tiles, which share input
     // pixels, go to the same one
@@ -657,7 +529,7 @@ __global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_step
             for (int v = 0; v < kV; ++v) px[st][v] = make_uint4(0, 0, 0, 0);
             if (ch * KS + st >= cls.steps) continue;        // uniform
             const ConvTab e = s_tab[4 * (cls.first + ch * KS + st) + q];
-            if ((unsigned)(r.y0 + e.dy) < (unsigned)SH && (unsigned)(r.x0 + e.dx) < (unsigned)SW) {
+            if (conv_reads<MODE>(S, r, e)) {
                 const uint4 *p =
                     MODE == kFwd ? reinterpret_cast<const uint4 *>(g.x + (r.base + e.off))
                                  : reinterpret_cast<const uint4 *>(g.dy + (r.base + e.off));
