@@ -247,6 +247,17 @@ def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def followed() -> bool:
+    """Whether torch follows the operations (transforms, forward-mode, tracing, dispatch and
+    function modes), so that a library call in their place would go unnoticed."""
+    import torch
+    return (torch._C._functorch.maybe_current_level() is not None
+            or torch.autograd.forward_ad._current_level >= 0
+            or torch._C._len_torch_dispatch_stack() > 0
+            or torch._C._len_torch_function_stack() > 0
+            or torch.jit.is_tracing() or torch.compiler.is_compiling())
+
+
 def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else C.c_void_p(0)
 

@@ -283,23 +283,15 @@ class TrainGraph:
         return self.z
 
 
-def _traced() -> bool:
-    """Whether torch follows the operations (transforms, forward-mode, tracing), so that a
-    library call would go unnoticed."""
-    torch = __import__("torch")
-    return (torch._C._functorch.maybe_current_level() is not None
-            or torch.autograd.forward_ad._current_level >= 0
-            or torch.jit.is_tracing() or torch.compiler.is_compiling())
-
-
 def decode(z, side=PATCH):
     """Raw outputs [n, 104] -> normalised curve parameters [n, 8, 13]:
     control points in patch sides (origin at the patch corner), then
     (width - 0.5) / 3.5, colour, opacity, each in [0, 1] for the last five."""
     torch = __import__("torch")
     if (type(z) is torch.Tensor and z.is_cuda and z.dtype == torch.float32 and z.is_contiguous()
+            and z.device.index == torch.cuda.current_device()
             and z.numel() > 0 and z.numel() % OUT == 0
-            and not (torch.is_grad_enabled() and z.requires_grad) and not _traced()):
+            and not (torch.is_grad_enabled() and z.requires_grad) and not bz.followed()):
         u = torch.empty((z.numel() // OUT, CURVES, PER_CURVE), dtype=z.dtype, device=z.device)
         bz._check("bz_decode", lib().bz_decode(_p(z), z.numel() // PER_CURVE, PER_CURVE, 8,
                                                1.0 + 2.0 * MARGIN, MARGIN, _p(u), bz._stream()))
