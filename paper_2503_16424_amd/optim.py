@@ -167,7 +167,7 @@ class Fitter:
     def push(self):
         """Parameters -> the rasterizer's curve buffers."""
         arrays = self._arrays()
-        if all(_plain(p, dst) for p, dst, _ in arrays):
+        if not bz.followed() and all(_plain(p, dst) for p, dst, _ in arrays):
             hx, hy = self._half
             _library("bz_affine_copy", [
                 bz.AffineGroup(dst.data_ptr(), p.data_ptr(), p.numel(), *a)
@@ -200,7 +200,8 @@ class Fitter:
         also makes the state, so the first update does), and so does a recording
         graph, whose step counts torch keeps on the host."""
         arrays = self._arrays()
-        if not (_plain_adam(self.opt, [p for p, _, _ in arrays])
+        if bz.followed() or not (
+                _plain_adam(self.opt, [p for p, _, _ in arrays])
                 and all(_plain(p, d) for p, _, d in arrays)):
             return False
         state = [self.opt.state.get(p, {}) for p, _, _ in arrays]

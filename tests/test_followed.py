@@ -63,3 +63,20 @@ def test_decode_on_another_device_is_left_to_torch(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_device", lambda: z.device.index + 1)
     monkeypatch.setattr(bz, "_check", lambda *a: pytest.fail("launched on another device"))
     assert torch.equal(cnn.decode(z), cnn.decode(z.clone().requires_grad_()).detach())
+
+
+@pytest.mark.gpu
+def test_fit_step_under_a_mode():
+    from paper_2503_16424_amd import optim, scenes
+    f = optim.Fitter(bz.Rasterizer(scenes.small_mixed(1)), optim.FitConfig())
+    for d in (f.rast.d_ctrl, f.rast.d_color, f.rast.d_opacity, f.rast.d_width):
+        d.fill_(1e-3)
+    f.update()                                              # makes the optimiser's state
+    assert f._update_in_one_launch()
+    with Dispatch() as mode:
+        f.update()
+        updated = len(mode.seen)
+        f.push()
+    seen = {str(op) for op in mode.seen}
+    assert any(s.startswith("aten.clamp_") for s in seen) and "aten.copy_.default" in seen
+    assert len(mode.seen) > updated
