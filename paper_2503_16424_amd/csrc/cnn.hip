@@ -518,7 +518,7 @@ __global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_step
         }
     }
     const int nc = g.N - n0 < 16 * NB ? g.N - n0 : 16 * NB;   // channels of this block
-    const int per_px = nc / kPer;               // 16-byte pieces of a pixel
+    const int per_px = conv_pieces<MODE>(nc);   // 16-byte pieces of a pixel
     const int px0 = lane / per_px, ch0 = lane - px0 * per_px;
     const bool via_lds = MODE == kBwdData || (g.out_b && g.N % kPer == 0);
 

@@ -89,6 +89,15 @@ __host__ __device__ inline ConvTab conv_tab(const GemmArgs &g, int k) {
 // Steps of 32 k.
 __host__ __device__ inline int conv_steps(int K) { return (K + 31) / 32; }
 
+// 16-byte pieces of nc output channels of a pixel (2 bytes each forward, 4 backward), for
+// blocks that store through LDS.  At least 1: a forward block of 4 channels has no whole
+// piece and stores its sums directly, but its lanes' places are divided all the same.
+template <int MODE>
+__host__ __device__ inline int conv_pieces(int nc) {
+    const int pieces = nc / (MODE == kFwd ? 8 : 4);
+    return pieces > 0 ? pieces : 1;
+}
+
 // Division of 0 <= m < 2^31 by d >= 1 without a divide per tile (Granlund and
 // Montgomery 1994): with 2^(s-1) < d <= 2^s and mul = ceil(2^(31+s) / d) < 2^32,
 // m / d = (m * mul) >> (31 + s).

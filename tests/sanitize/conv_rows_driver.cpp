@@ -62,6 +62,22 @@ static long replay(const Shape &S, int classes, long *reads) {
     return bad;
 }
 
+// The lanes' first 16-byte pieces in every block of 16 nb output channels of n: pixel and
+// piece inside the tile (the sanitizer sees a division by zero).
+template <int MODE>
+static long pieces(int n, int nb) {
+    long bad = 0;
+    for (int n0 = 0; n0 < n; n0 += 16 * nb) {
+        const int nc = n - n0 < 16 * nb ? n - n0 : 16 * nb;
+        const int per = conv_pieces<MODE>(nc);
+        for (int lane = 0; lane < 64; ++lane)
+            bad += lane / per * per + lane % per != lane;
+        if (nc * (MODE == kFwd ? 2 : 4) % 16 == 0)
+            bad += per * 16 != nc * (MODE == kFwd ? 2 : 4);
+    }
+    return bad;
+}
+
 int main(int argc, char **argv) {
     if (argc != 9) return 2;
     int v[8];
@@ -72,6 +88,10 @@ int main(int argc, char **argv) {
     long fwd = 0, bwd = 0, bad_bwd = 0;
     const long bad_fwd = replay<kFwd>(S, 1, &fwd);
     if (S.k % 8 == 0) bad_bwd = replay<kBwdData>(S, S.s * S.s, &bwd);
+    for (int nb = 1; nb <= 4; nb += 3) {
+        bad_bwd += pieces<kBwdData>(S.c, nb);
+        if (pieces<kFwd>(S.k, nb)) return 3;
+    }
     printf("forward: %ld reads, %ld wrong; input gradient: %ld reads, %ld wrong\n", fwd, bad_fwd, bwd,
            bad_bwd);
     return bad_fwd || bad_bwd;

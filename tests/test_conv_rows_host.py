@@ -30,6 +30,8 @@ SHAPES = [  # n, h, w, c, k, r, stride, pad
     (5, 7, 9, 16, 24, 3, 3, 2),
     (1, 1, 1, 8, 8, 1, 1, 0),
     (2, 4, 6, 32, 32, 3, 2, 0),
+    (2, 5, 5, 8, 4, 3, 1, 1),          # 4 output channels in a block: 4, 16 + 4, 64 + 4
+    (2, 5, 5, 8, 20, 1, 1, 0),
 ]
 
 
