@@ -674,34 +674,59 @@ bool conv_rows_serves(const GemmArgs &g) {
            aligned(g.out_f, 16) && aligned(g.out_b, 16) && aligned(g.mask, 8);
 }
 
+// Workgroups of a vector convolution: waves per block and blocks per column and class.
+struct ConvGrid {
+    int waves;
+    size_t lds;
+    int64_t gx, most;           // blocks wanted (one row tile per wave), resident
+};
+
+template <int MODE>
+ConvGrid conv_grid(int64_t rows, int64_t n, int64_t steps, int classes, int groups, int nb) {
+    constexpr int kOutB = MODE == kFwd ? 2 : 4;
+    ConvGrid c;
+    // the filters' LDS decides how many blocks a CU holds: 16 waves in one block
+    // where two blocks do not fit
+    c.waves = conv_rows_lds(steps, classes, nb, kOutB, 8) > 80 * 1024 ? 16 : 8;
+    c.lds = conv_rows_lds(steps, classes, nb, kOutB, c.waves);
+    const int64_t per_cu = c.lds > 80 * 1024 || c.waves == 16 ? 1 : c.lds > 53 * 1024 ? 2 : 3;
+    c.gx = cdiv(cdiv(rows, 16), c.waves);
+    // rounded down: two blocks more than the chip holds run alone at the end (384 to 384
+    // channels, 1 x 1, 65,536 pixels: 171 us for the input gradient)
+    c.most = 256 * per_cu / (cdiv(n, 16 * nb) * groups);
+    if (c.most < 1) c.most = 1;
+    return c;
+}
+
 template <int MODE, int NB>
 void launch_conv_rows(const GemmArgs &g, int64_t rows, int steps, int classes, int groups,
                       hipStream_t s) {
-    constexpr int kOutB = MODE == kFwd ? 2 : 4;
-    const int64_t tiles = cdiv(rows, 16), cols = cdiv(g.N, 16 * NB);
-    // the filters' LDS decides how many blocks a CU holds: 16 waves in one block
-    // where two blocks do not fit
-    const int waves = conv_rows_lds(steps, classes, NB, kOutB, 8) > 80 * 1024 ? 16 : 8;
-    const size_t lds = conv_rows_lds(steps, classes, NB, kOutB, waves);
+    const ConvGrid c = conv_grid<MODE>(rows, g.N, steps, classes, groups, NB);
     // resident blocks only: a wave takes several tiles, its filters loaded once
-    const int64_t per_cu = lds > 80 * 1024 || waves == 16 ? 1 : lds > 53 * 1024 ? 2 : 3;
-    int64_t gx = cdiv(tiles, waves);
-    const int64_t most = cdiv(256 * per_cu, cols * groups);
-    if (gx > most) gx = most;
-    hipLaunchKernelGGL((k_conv_rows<MODE, NB>), dim3((unsigned)gx, (unsigned)cols, (unsigned)groups),
-                       dim3(64 * waves), lds, s, g, steps, classes);
+    hipLaunchKernelGGL((k_conv_rows<MODE, NB>),
+                       dim3((unsigned)(c.gx < c.most ? c.gx : c.most),
+                            (unsigned)cdiv(g.N, 16 * NB), (unsigned)groups),
+                       dim3(64 * c.waves), c.lds, s, g, steps, classes);
 }
 
 // rows: output pixels, or blocks of stride x stride input pixels.  Steps of 32 k:
-// over all classes, and in the class with most.  False: the filters of 16 output
-// channels do not fit.
+// over all classes, and in the class with most.  False: k_igemm is to be used.
 //
 // A block takes 64 output channels and, for the input gradient, all classes of its
 // pixel blocks (their output gradients are then read once, and no class's waves
 // end early: 163 -> 147 us for the second layer at 1024 images against a class per
-// block).  Where that would leave CUs without a block it takes one class, and
-// below that 16 channels
-// (all classes together there: the third layer at 256 images 14 -> 23 us).
+// block).  Where that would leave CUs without a block, or the filters do not fit, it takes
+// one class, and below that 16 channels (all classes together there: the third layer at
+// 256 images 14 -> 23 us).
+//
+// With 16 channels a block each pixel is read by n / 16 blocks, where k_igemm's read it
+// n / 64 times.  That pays while 64-channel blocks would be few (narrow_pays): 128 to 128
+// channels, 3 x 3, input gradient, 47 -> 20 us at 4,096 pixels, but 58 -> 90 at 16,384
+// and 134 -> 255 at 65,536 (forward 21 -> 12, 24 -> 50, 54 -> 133; 384 channels at
+// 65,536 pixels 409 -> 1,873).  Up to 128 such blocks it was always at least even; above,
+// where the 16-channel blocks are all resident at once: 256 to 256 at 4,096 pixels (128
+// wide blocks) 86 -> 61, 96 to 96 at 16,384 (256 of them) 19 -> 16, but 19 -> 22 with a
+// stride of 2, whose rows lie apart, hence the bound of 192 there.
 template <int MODE>
 bool try_conv_rows(const GemmArgs &g, int64_t rows, int64_t steps, int64_t longest, int classes,
                    hipStream_t s) {
@@ -709,11 +734,15 @@ bool try_conv_rows(const GemmArgs &g, int64_t rows, int64_t steps, int64_t longe
     constexpr size_t kMost = 144 * 1024;
     if (!conv_rows_serves<MODE>(g) || longest > 4096) return false;
     const int64_t wide = cdiv(rows, 16 * 8) * cdiv(g.N, 64);
+    const auto narrow_pays = [&] {
+        const ConvGrid c = conv_grid<MODE>(rows, g.N, longest, 1, classes, 1);
+        return wide < 128 || (c.gx <= c.most && (wide < 192 || g.S.s == 1));
+    };
     if (wide >= 192 && conv_rows_lds(steps, classes, 4, kOutB, 16) <= kMost)
         launch_conv_rows<MODE, 4>(g, rows, (int)steps, classes, 1, s);
     else if (wide * classes >= 192 && conv_rows_lds(longest, 1, 4, kOutB, 16) <= kMost)
         launch_conv_rows<MODE, 4>(g, rows, (int)longest, 1, classes, s);
-    else if (conv_rows_lds(longest, 1, 1, kOutB, 16) <= kMost)
+    else if (conv_rows_lds(longest, 1, 1, kOutB, 16) <= kMost && narrow_pays())
         launch_conv_rows<MODE, 1>(g, rows, (int)longest, 1, classes, s);
     else
         return false;
