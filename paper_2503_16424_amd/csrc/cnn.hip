@@ -779,12 +779,21 @@ __global__ __launch_bounds__(256) void k_wgrad(GemmArgs g, float *db) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int cg = t & 7, pg = t >> 3;          // 8 channels, 4 pixels
     // workgroup b runs on XCD b % 8: the tiles of a chunk of pixels, which read the
-    // same operands, on one XCD
+    // same operands, on one XCD; fewer than eight chunks over all XCDs, tile by tile
+    // (512 to 512 channels, 3 x 3, two chunks: 947 us on two XCDs)
     const int tm = (g.M + 63) / 64, tn = (g.N + 63) / 64, tiles = tm * tn;
-    const int b8 = (int)blockIdx.x / (8 * tiles), in8 = (int)blockIdx.x - b8 * 8 * tiles;
-    const int tile = in8 / 8, m0 = (tile % tm) * 64, n0 = (tile / tm) * 64;
-    const int chunk = b8 * 8 + in8 % 8, chunks = (g.K + g.k_chunk - 1) / g.k_chunk;
-    if (chunk >= chunks) return;
+    const int chunks = (g.K + g.k_chunk - 1) / g.k_chunk;
+    int tile, chunk;
+    if (chunks >= 8) {
+        const int b8 = (int)blockIdx.x / (8 * tiles), in8 = (int)blockIdx.x - b8 * 8 * tiles;
+        tile = in8 / 8;
+        chunk = b8 * 8 + in8 % 8;
+        if (chunk >= chunks) return;
+    } else {
+        chunk = (int)blockIdx.x / tiles;
+        tile = (int)blockIdx.x - chunk * tiles;
+    }
+    const int m0 = (tile % tm) * 64, n0 = (tile / tm) * 64;
     const int kbeg = chunk * g.k_chunk;
     const int kend = kbeg + g.k_chunk < g.K ? kbeg + g.k_chunk : g.K;
     const int co = m0 + 8 * cg, n = n0 + 8 * cg;
@@ -1333,8 +1342,9 @@ hipError_t launch_conv_bwd_weight(const bz_conv &c, const float *dy, const uint1
         int64_t splits = cdiv(kWgGroups, tiles);
         if (g.K > 1024 * splits) splits *= 2;
         g.k_chunk = (int)(cdiv(cdiv(g.K, splits), kWgPix) * kWgPix);
-        const int64_t chunks8 = cdiv(cdiv(g.K, g.k_chunk), 8) * 8;
-        hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(tiles * chunks8)), dim3(256), 0, s, g, db);
+        const int64_t chunks = cdiv(g.K, g.k_chunk);
+        hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(tiles * (chunks >= 8 ? cdiv(chunks, 8) * 8 : chunks))),
+                           dim3(256), 0, s, g, db);
         return hipGetLastError();
     }
     g.k_chunk = cdiv(g.K, kSplitRows) * tiles < kSplitMinGroups ? kSplitRowsSmall : kSplitRows;
