@@ -818,7 +818,8 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
     const float4 *__restrict__ rec, const ushort4 *__restrict__ rects, int64_t n, int W, int H,
     int tiles_x, float inv_tw, int th, float two_p, const bz_canvas *__restrict__ cv,
     int n_canvas, const uint32_t *__restrict__ bucket, int nbk, int64_t n_eblk,
-    uint32_t *__restrict__ packed, uint32_t *__restrict__ seg, int64_t *status) {
+    uint32_t *__restrict__ packed, uint32_t *__restrict__ seg, uint32_t *__restrict__ sums,
+    int64_t n_sums, int64_t *status) {
     static_assert(kEmitBlock == kEmitG, "one emission block per wave");
     __shared__ uint32_t s_rows[kEmitWaves][kEmitG + 1];   // exclusive prefix of tile rows
     __shared__ SupportLds s_sup[kEmitWaves][kEmitG];
@@ -835,6 +836,10 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
     __shared__ uint2 s_pe[kEmitWaves][kMaxBk];   // (pos, end), one 8-byte read
     if (status[1] & Status::kOverflow) return;
     const int t = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // the long buckets' sums start at zero (n_sums: 0 where no bucket can be long)
+    for (int64_t i = (int64_t)blockIdx.x * (64 * kEmitWaves) + threadIdx.x; i < n_sums;
+         i += (int64_t)gridDim.x * (64 * kEmitWaves))
+        sums[i] = 0u;
     if (blockIdx.x == 0 && wv == 0) segment_table(bucket, nbk, n_eblk, (uint32_t)status[0], t, seg);
     const int64_t per = (n_eblk + 8 * kEmitWaves - 1) / (8 * kEmitWaves);   // workgroups per XCD
     const int64_t eb = ((int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3)) * kEmitWaves + wv;
@@ -1025,34 +1030,40 @@ __device__ inline int seg_find(const uint32_t *P, int nbk, uint32_t b) {
     return lo;
 }
 
-// A radix block of the in-bucket pass: its segment, its first element and
-// count, and where its digit counts are in hseg: [block][digit] where each bucket
-// is scanned by itself (alone), bucket by bucket [digit][block] for the device-wide
-// scan.
+// A radix block of the in-bucket pass: its segment, its first element and count, and
+// the index of its digit-0 count in hseg ([block][digit]).
 struct SegBlock {
     uint32_t pos0, cnt;
-    int64_t h0;        // hseg index of (segment, digit 0, this block)
-    uint32_t hs;       // stride between digits
+    int64_t h0;
+    int seg;
+    uint32_t j;        // block of the segment
     bool real;
 };
 
-__device__ inline SegBlock seg_block(const uint32_t *s_S, const uint32_t *s_P, int nbk, uint32_t b,
-                                     bool alone) {
+__device__ inline SegBlock seg_block(const uint32_t *s_S, const uint32_t *s_P, int nbk, uint32_t b) {
     SegBlock r;
     r.real = b < s_P[nbk];
-    if (!r.real) {
-        r.pos0 = r.cnt = 0;
-        r.hs = 1;
-        r.h0 = (int64_t)b * kRadix;
-        return r;
-    }
-    const int s = seg_find(s_P, nbk, b);
-    const uint32_t j = b - s_P[s];
-    r.pos0 = s_S[s] + j * (uint32_t)kTile;
-    r.cnt = min((uint32_t)kTile, s_S[s + 1] - r.pos0);
-    r.hs = alone ? 1u : s_P[s + 1] - s_P[s];
-    r.h0 = alone ? (int64_t)kRadix * b : (int64_t)kRadix * s_P[s] + j;
+    r.h0 = (int64_t)b * kRadix;
+    r.pos0 = r.cnt = r.j = 0;
+    r.seg = 0;
+    if (!r.real) return r;
+    r.seg = seg_find(s_P, nbk, b);
+    r.j = b - s_P[r.seg];
+    r.pos0 = s_S[r.seg] + r.j * (uint32_t)kTile;
+    r.cnt = min((uint32_t)kTile, s_S[r.seg + 1] - r.pos0);
     return r;
+}
+
+// Buckets of more than kSuper radix blocks are long: the digit counts of every kSuper
+// consecutive blocks of theirs are also summed (sums, [super][digit]), so that workgroups
+// can scan the supers of a bucket side by side.  Row of super i of bucket b, whose first
+// block is P: rows of different buckets never meet.
+constexpr int kSuper = 256;
+__host__ __device__ inline int64_t super_rows(int64_t blocks, int64_t nbk) {
+    return blocks / kSuper + nbk + 1;
+}
+__device__ inline uint32_t super_row(uint32_t P, int b, uint32_t i) {
+    return P / kSuper + (uint32_t)b + i;
 }
 
 __device__ inline void load_seg(const uint32_t *seg, int nbk, uint32_t *s_S, uint32_t *s_P) {
@@ -1062,12 +1073,11 @@ __device__ inline void load_seg(const uint32_t *seg, int nbk, uint32_t *s_S, uin
     }
 }
 
-// Digit counts of one radix block of the in-bucket pass (low key byte).  alone:
-// each bucket's counts are scanned by themselves (k_seg_scan), so blocks past the
-// last bucket's leave no zeros.
+// Digit counts of one radix block of the in-bucket pass (low key byte); those of a
+// long bucket are added to its sums (null: no bucket can be long).
 __global__ __launch_bounds__(256) void k_seg_hist(const uint32_t *__restrict__ packed,
                                                   const uint32_t *__restrict__ seg, int nbk,
-                                                  const int64_t *status, bool alone,
+                                                  const int64_t *status, uint32_t *sums,
                                                   uint32_t *__restrict__ hseg) {
     __shared__ uint32_t h[kRadix];
     __shared__ uint32_t s_S[kRadix + 1], s_P[kRadix + 1];
@@ -1076,76 +1086,109 @@ __global__ __launch_bounds__(256) void k_seg_hist(const uint32_t *__restrict__ p
     load_seg(seg, nbk, s_S, s_P);
     h[t] = 0u;
     __syncthreads();
-    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x, alone);
-    if (!sb.real && alone) return;             // uniform over the block
+    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x);
+    if (!sb.real) return;                      // uniform over the block
     // consecutive pairs of a bucket are mostly consecutive keys: no runs of
     // equal digits to add at once, so one LDS atomic per pair
     for (uint32_t i = t; i < sb.cnt; i += kBlk) atomicAdd(&h[packed[sb.pos0 + i] >> 24], 1u);
     __syncthreads();
-    hseg[sb.h0 + (int64_t)t * sb.hs] = h[t];
+    hseg[sb.h0 + t] = h[t];
+    if (sums && s_P[sb.seg + 1] - s_P[sb.seg] > (uint32_t)kSuper && h[t])
+        atomicAdd(&sums[(int64_t)kRadix * super_row(s_P[sb.seg], sb.seg, sb.j / kSuper) + t], h[t]);
 }
 
 // Positions of one bucket's (digit, radix block) parts from its first position, over
-// the counts in place: one workgroup per bucket, thread (part p, digit d) taking a
-// quarter of the blocks, 1 KiB rows at a time.  Counts laid out by block, not by digit:
-// there a radix block wrote its 256 counts into as many lines, shared with blocks on
-// other XCDs (7.2 M pairs: counts and scan 12.5 + 12.6 us that way, 9.1 + 9.8 this way;
-// 33.7 M pairs, whose counts were 69 MB of partial lines for 10 MB, 66 + 14 and 55 +
-// 9.5).  Bound by latency: one read of up to 64 blocks' rows 4.0-4.7 us.
+// the counts in place.  Workgroup (b, y) takes supers y, y + gridDim.y, ... of bucket b
+// (a short bucket is one): thread (part p, digit d) a quarter of its blocks, 1 KiB rows
+// at a time, which stay in registers between the sum and the positions.  A long bucket's
+// totals, and what lies before the super, come from the sums that k_seg_hist took, so no
+// workgroup reads counts that another one overwrites.
+// Counts laid out by block, not by digit: there a radix block wrote its 256 counts into
+// as many lines, shared with blocks on other XCDs (33.7 M pairs, whose counts were 69 MB
+// of partial lines for 10 MB: counts and scan over the whole device 66 + 14 us, this way
+// 55 + 9.5).  Bound by latency: 3.7-4.9 us where no bucket is long.  A bucket of 8,500
+// blocks (34.8 M pairs in two tile rows of a 2048x2048 frame), scanned by one workgroup,
+// took 332 us, in supers by eight 39, and its counts 71 instead of 62; 3 M pairs 30 -> 8.
+constexpr int kScanSlices = 8;
+
 __global__ __launch_bounds__(kOneThreads) void k_seg_scan(const uint32_t *__restrict__ seg, int nbk,
-                                                          const int64_t *status, uint32_t *hseg) {
-    constexpr int kParts = kOneThreads / kRadix;
-    __shared__ uint32_t s_sum[kParts][kRadix];
+                                                          const int64_t *status,
+                                                          const uint32_t *__restrict__ sums,
+                                                          uint32_t *hseg) {
+    constexpr int kParts = kOneThreads / kRadix, kRounds = kSuper / (kParts * kItems);
+    __shared__ uint32_t s_sum[kParts][kRadix], s_all[kParts][kRadix], s_front[kParts][kRadix];
     __shared__ uint32_t s_wave[kRadix / 64];
     if (status[1] & Status::kOverflow) return;
-    const int b = blockIdx.x, d = threadIdx.x % kRadix, p = threadIdx.x / kRadix;
+    const int b = blockIdx.x, d = threadIdx.x % kRadix;
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / kRadix);
     const uint32_t P = seg[nbk + 1 + b], nbs = seg[nbk + 2 + b] - P;
-    const uint32_t per = (nbs + kParts - 1) / kParts;
-    const uint32_t r0 = min(p * per, nbs), r1 = min(r0 + per, nbs);
-    uint32_t *h = hseg + (int64_t)kRadix * P + d;
-    uint32_t x[kItems], sum = 0;
-    for (uint32_t r = r0; r < r1; r += kItems) {
+    const uint32_t supers = (nbs + kSuper - 1) / kSuper;
+    for (uint32_t i = blockIdx.y; i < supers; i += gridDim.y) {
+        const uint32_t n = min(nbs - i * kSuper, (uint32_t)kSuper);
+        const uint32_t per = (n + kParts - 1) / kParts;
+        const uint32_t r0 = min(p * per, n), r1 = min(r0 + per, n);
+        uint32_t *h = hseg + (int64_t)kRadix * (P + i * kSuper) + d;
+        uint32_t x[kRounds][kItems], sum = 0;
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) x[j] = r + j < r1 ? h[(int64_t)kRadix * (r + j)] : 0u;
+        for (int c = 0; c < kRounds; ++c) {
+            if (r0 + kItems * c >= r1) continue;               // uniform over the wave
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) sum += x[j];
-    }
-    s_sum[p][d] = sum;
-    __syncthreads();
-    uint32_t before = 0, total = 0;             // of digit d: the parts before p, all
-#pragma unroll
-    for (int i = 0; i < kParts; ++i) {
-        const uint32_t v = s_sum[i][d];
-        if (i < p) before += v;
-        total += v;
-    }
-    uint32_t tot;                               // digits of this wave, in digit order
-    uint32_t at = wave_excl_scan(total, tot);
-    if (p == 0 && (d & 63) == 63) s_wave[d >> 6] = tot;
-    __syncthreads();
-    for (int i = 0; i < (d >> 6); ++i) at += s_wave[i];
-    at += seg[b] + before;
-    const bool held = per <= kItems;            // the counts are still in registers
-    for (uint32_t r = r0; r < r1; r += kItems) {
-        if (!held) {
-#pragma unroll
-            for (int j = 0; j < kItems; ++j) x[j] = r + j < r1 ? h[(int64_t)kRadix * (r + j)] : 0u;
+            for (int j = 0; j < kItems; ++j) {
+                const uint32_t r = r0 + kItems * c + j;
+                x[c][j] = r < r1 ? h[(int64_t)kRadix * r] : 0u;
+            }
+        }
+        uint32_t all = 0, front = 0;
+        if (supers > 1) {
+            const uint32_t *q = sums + (int64_t)kRadix * super_row(P, b, 0) + d;
+#pragma unroll 8
+            for (uint32_t k = p; k < supers; k += kParts) {
+                const uint32_t v = q[(int64_t)kRadix * k];
+                all += v;
+                if (k < i) front += v;
+            }
         }
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) {
-            if (r + j < r1) h[(int64_t)kRadix * (r + j)] = at;
-            at += x[j];
+        for (int c = 0; c < kRounds; ++c) {
+            if (r0 + kItems * c >= r1) continue;
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) sum += x[c][j];
+        }
+        s_sum[p][d] = sum;
+        if (supers > 1) {
+            s_all[p][d] = all;
+            s_front[p][d] = front;
+        }
+        __syncthreads();
+        uint32_t before = 0, total = 0;         // of digit d: what lies before, all
+#pragma unroll
+        for (uint32_t k = 0; k < (uint32_t)kParts; ++k) {
+            const uint32_t v = s_sum[k][d];
+            if (k < p) before += v;
+            if (supers > 1) {
+                total += s_all[k][d];
+                before += s_front[k][d];
+            } else {
+                total += v;
+            }
+        }
+        uint32_t tot;                           // digits of this wave, in digit order
+        uint32_t at = wave_excl_scan(total, tot);
+        if (p == 0 && (d & 63) == 63) s_wave[d >> 6] = tot;
+        __syncthreads();
+        for (int k = 0; k < (d >> 6); ++k) at += s_wave[k];
+        at += seg[b] + before;
+#pragma unroll
+        for (int c = 0; c < kRounds; ++c) {
+            if (r0 + kItems * c >= r1) continue;
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) {
+                const uint32_t r = r0 + kItems * c + j;
+                if (r < r1) h[(int64_t)kRadix * r] = at;
+                at += x[c][j];
+            }
         }
     }
-}
-
-// Whether each bucket's counts are scanned by one workgroup, which takes two rounds of
-// about 1 us for every 64 of its radix blocks after the first 64: up to 256 blocks per
-// bucket on average (a batch whose canvases fill some buckets far more than others
-// 9.8 us against 11; 33.7 M pairs in 64 buckets 9.5 against 14), and up to 512 in all,
-// where the longest bucket cannot take more than 16 rounds.
-inline bool seg_alone(const BinLayout &L) {
-    return L.seg_blocks <= 512 || L.seg_blocks <= 256 * L.n_buckets;
 }
 
 // The in-bucket pass's scatter: ranks as in k_radix_scatter (digit = key
@@ -1157,8 +1200,7 @@ inline bool seg_alone(const BinLayout &L) {
 __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict__ packed,
                                                      const uint32_t *__restrict__ seg, int nbk,
                                                      const uint32_t *__restrict__ hseg,
-                                                     const int64_t *status, bool alone,
-                                                     uint32_t n_tiles,
+                                                     const int64_t *status, uint32_t n_tiles,
                                                      uint32_t *__restrict__ ranges,
                                                      uint32_t *__restrict__ ids) {
     __shared__ uint32_t s_keys[kTile];
@@ -1181,15 +1223,15 @@ __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict_
         const uint32_t b = blockIdx.x, nbs = s_P[b + 1] - s_P[b];
         uint32_t first = 0, end = 0;
         if (nbs) {
-            const int64_t h0 = (int64_t)kRadix * s_P[b], hs = alone ? 1 : nbs;
-            first = hseg[h0 + tid * hs];
-            end = tid < kRadix - 1 ? hseg[h0 + (tid + 1) * hs] : s_S[b + 1];
+            const int64_t h0 = (int64_t)kRadix * s_P[b];
+            first = hseg[h0 + tid];
+            end = tid < kRadix - 1 ? hseg[h0 + tid + 1] : s_S[b + 1];
             if (first == end) first = end = 0u;
         }
         ranges[2 * (int64_t)tile] = first;
         ranges[2 * (int64_t)tile + 1] = end;
     }
-    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x, alone);
+    const SegBlock sb = seg_block(s_S, s_P, nbk, blockIdx.x);
     if (!sb.real) return;                      // uniform over the block
     const int cnt = (int)sb.cnt;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -1228,7 +1270,7 @@ __global__ __launch_bounds__(256) void k_seg_scatter(const uint32_t *__restrict_
             s_wrun[q][tid] = r;
             r += c[q];
         }
-        s_goff[tid] = hseg[sb.h0 + (int64_t)tid * sb.hs] - prefix;
+        s_goff[tid] = hseg[sb.h0 + tid] - prefix;
     }
     __syncthreads();
 #pragma unroll
@@ -1308,8 +1350,7 @@ BinLayout bin_layout(const bz_opts &o, int64_t n_gauss, int64_t cap) {
         L.off_hseg = off;
         off = align256(off + 4 * kRadix * L.seg_blocks);
         L.off_part = off;
-        const int64_t pa = cdiv(L.n_buckets * L.n_eblk, kTile), pb = cdiv(kRadix * L.seg_blocks, kTile);
-        off = align256(off + 8 * (pa > pb ? pa : pb));
+        off = align256(off + 8 * cdiv(L.n_buckets * L.n_eblk, kTile));
         L.total = off;
         return L;
     }
@@ -1404,25 +1445,29 @@ hipError_t bin_finish_fused(const float *rec, const BinBufs &u, int64_t n, const
     hipError_t e = scan_u32(u.bucket, u.bucket, L.n_buckets * L.n_eblk, u.part, b.status,
                             b.cap_pairs, b.status, s);
     if (e != hipSuccess) return e;
+    // The long buckets' sums lie in the ids, which nothing reads before the scatter
+    // writes them: from kSuper radix blocks of pairs on there is room for them (at most
+    // a 4096th of the capacity and 66,560 words).
+    const bool can_be_long = b.cap_pairs > (int64_t)kSuper * kTile;
+    const int64_t n_sums = can_be_long ? kRadix * super_rows(L.seg_blocks, nbk) : 0;
+    uint32_t *sums =
+        can_be_long ? (uint32_t *)(((uintptr_t)b.ids + 15) & ~(uintptr_t)15) : nullptr;
     // a smaller bucket table in LDS when it fits: more waves per CU
     hipLaunchKernelGGL(nbk <= 64 ? k_emit_bucketed<64> : k_emit_bucketed<256>,
                        dim3(8 * cdiv(L.n_eblk, 8 * kEmitWaves)), dim3(64 * kEmitWaves), 0, s,
                        (const float4 *)rec, (const ushort4 *)u.rects, n, o.width, o.height,
                        (int)tiles_x(o), 1.0f / o.tile_w, o.tile_h, support_two_p(o), cv, ncv,
-                       (const uint32_t *)u.bucket, nbk, L.n_eblk, u.packed, u.seg, b.status);
-    const bool alone = seg_alone(L);
+                       (const uint32_t *)u.bucket, nbk, L.n_eblk, u.packed, u.seg, sums, n_sums,
+                       b.status);
     hipLaunchKernelGGL(k_seg_hist, dim3(L.seg_blocks), dim3(kBlk), 0, s,
                        (const uint32_t *)u.packed, (const uint32_t *)u.seg, nbk,
-                       (const int64_t *)b.status, alone, u.hseg);
-    if (alone)
-        hipLaunchKernelGGL(k_seg_scan, dim3(nbk), dim3(kOneThreads), 0, s,
-                           (const uint32_t *)u.seg, nbk, (const int64_t *)b.status, u.hseg);
-    else
-        e = scan_u32(u.hseg, u.hseg, kRadix * L.seg_blocks, u.part, nullptr, 0, b.status, s);
-    if (e != hipSuccess) return e;
+                       (const int64_t *)b.status, sums, u.hseg);
+    hipLaunchKernelGGL(k_seg_scan, dim3(nbk, can_be_long ? kScanSlices : 1), dim3(kOneThreads), 0,
+                       s, (const uint32_t *)u.seg, nbk, (const int64_t *)b.status,
+                       (const uint32_t *)sums, u.hseg);
     hipLaunchKernelGGL(k_seg_scatter, dim3(L.seg_blocks), dim3(kBlk), 0, s,
                        (const uint32_t *)u.packed, (const uint32_t *)u.seg, nbk,
-                       (const uint32_t *)u.hseg, (const int64_t *)b.status, alone, (uint32_t)L.n_tiles,
+                       (const uint32_t *)u.hseg, (const int64_t *)b.status, (uint32_t)L.n_tiles,
                        b.ranges, b.ids);
     return hipGetLastError();
 }
