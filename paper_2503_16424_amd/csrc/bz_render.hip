@@ -1742,10 +1742,12 @@ void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, f
                            gr.d_opacity);
     }
     if (c.max_gauss_per_curve <= 32 && c.n_curves >= kShareCurves) {
+        // K is at most the Gaussian count, however loose a bound max_k is
         const int share = c.max_gauss_per_curve <= 16 ? 4 : 2;
-        const int64_t lds = share * stage2_lds_bytes(c.max_k, c.max_gauss_per_curve);
+        const int lk = c.max_k < c.max_gauss_per_curve ? c.max_k : c.max_gauss_per_curve;
+        const int64_t lds = share * stage2_lds_bytes(lk, c.max_gauss_per_curve);
         hipLaunchKernelGGL((share == 4 ? k_bwd_curves<16, kPacked> : k_bwd_curves<32, kPacked>),
-                           dim3((c.n_curves + share - 1) / share), dim3(kWave), lds, s, c, c.max_k,
+                           dim3((c.n_curves + share - 1) / share), dim3(kWave), lds, s, c, lk,
                            c.max_gauss_per_curve, inv_rho2, s0, d_gauss, planes, c.n_gauss,
                            gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
         return;
