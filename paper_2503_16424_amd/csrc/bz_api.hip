@@ -383,7 +383,7 @@ bz_status bz_render_bwd_curves(const bz_curves *c, const bz_opts *o, const float
     bz_status st = check_bwd_curves(c, o, d_gauss, gr);
     if (st != BZ_OK) return st;
     (void)hipGetLastError();
-    return launched(launch_bwd_curves(*c, *o, d_gauss, nullptr, *gr, s));
+    return launched(launch_bwd_curves(*c, *o, nullptr, d_gauss, nullptr, *gr, s));
 }
 
 bz_status bz_render_bwd(const bz_curves *c, const bz_gaussians *g, const bz_bins *b,
@@ -430,7 +430,7 @@ bz_status bz_render_bwd_scratch(const bz_curves *c, const bz_gaussians *g, const
     (void)hipGetLastError();
     st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s));
     if (st != BZ_OK) return st;
-    return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
+    return launched(launch_bwd_curves(*c, *o, g->rec, scratch, gr->d_gauss, *gr, s));
 }
 
 bz_status bz_step(const bz_curves *c, const bz_opts *o, bz_gaussians *g, bz_bins *b, float *image,
@@ -458,7 +458,7 @@ bz_status bz_step(const bz_curves *c, const bz_opts *o, bz_gaussians *g, bz_bins
     st = launched(launch_bwd_gauss(g->rec, g->n, *b, *o, d_image, state, scratch, true, s,
                                    cleared && few));
     if (st != BZ_OK) return st;
-    return launched(launch_bwd_curves(*c, *o, scratch, gr->d_gauss, *gr, s));
+    return launched(launch_bwd_curves(*c, *o, g->rec, scratch, gr->d_gauss, *gr, s));
 }
 
 bz_status bz_curve_area(const bz_curves *c, float *area, hipStream_t s) {

@@ -106,10 +106,11 @@ hipError_t launch_fwd(const float *rec, const bz_bins &b, const bz_opts &o, floa
 hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
                             const bz_opts &o, const float *d_image, const bz_pixstate *st,
                             float *d_gauss, bool packed, hipStream_t s, bool cleared = false);
-// planes non-null: d_gauss is packed (9 floats per Gaussian) and the planes are
-// written too.
-hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,
-                             float *planes, const bz_grads &gr, hipStream_t s);
+// planes non-null: d_gauss is packed (9 floats per Gaussian), the planes are
+// written too, and rec is the records the first stage ran on.
+hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *rec,
+                             const float *d_gauss, float *planes, const bz_grads &gr,
+                             hipStream_t s);
 hipError_t launch_l2(const float *image, const float *target, int64_t n, float scale,
                      float *d_image, float *loss, hipStream_t s);
 hipError_t launch_area(const bz_curves &c, float *area, hipStream_t s);

@@ -1184,6 +1184,22 @@ __device__ inline float lanes_sum(float v) {
     return v;
 }
 
+// X[r][k1] - X[r][k0] from the samples in double precision, as the sampler has them,
+// rounded once; t: the row's place between the boundaries.
+__device__ inline float2 chord_between(const CurveView &v, double t, int k0, int k1) {
+    double2 first = make_double2(0.0, 0.0), x = first;
+#pragma unroll 1
+    for (int e = 0; e < 2; ++e) {
+        first = x;
+        x = boundary_point(v, false, e ? k1 : k0);
+        if (v.kind == BZ_CLOSED) {
+            const double2 b = boundary_point(v, true, e ? k1 : k0);
+            x = make_double2((1.0 - t) * x.x + t * b.x, (1.0 - t) * x.y + t * b.y);
+        }
+    }
+    return make_float2((float)(x.x - first.x), (float)(x.y - first.y));
+}
+
 // Stage 2: one workgroup per curve.  Per Gaussian (r, k) the gradients of
 // (mean, Q, o, colour) are chained to the sample points of its stencil:
 //   Q = R diag(a, b) R^T, a = 1/sx2, b = 1/sy2, (c, s) = v/|v|,
@@ -1197,7 +1213,11 @@ __device__ inline float lanes_sum(float v) {
 // The boundary samples are evaluated in double precision (coordinates of
 // thousands of pixels) and only their differences along each boundary and
 // from boundary A to B are kept, rounded to float (differences of a pixel):
-// a row's differences are blends of those, and the chain itself is float.
+// a row's differences are blends of those, and the chain itself is float.  Where a row
+// turns back on itself its tangent, the difference over two columns, nearly cancels, and
+// with the rounding of the chords it is made of so does its direction, in which the
+// conic's gradient is turned: below 1% of the chords the direction is the record's
+// (kPacked, one load), or the tangent is taken anew from the samples in double precision.
 //
 // NT threads per curve.  Two launches split the curves by size: those of at
 // most kSmallCurve Gaussians (open strokes) run as one-wave workgroups with
@@ -1205,16 +1225,17 @@ __device__ inline float lanes_sum(float v) {
 // skips the other's curves.  Where no curve has more than 32 (16) Gaussians and the
 // chip is full, two (four) share a wave: 35,000 strokes of 16 to 32 samples 62 -> 50 us.  lk and lg are the K and Gaussian capacities the
 // dynamic LDS is laid out for.
-// Eight waves per SIMD (at most 64 VGPRs; 49 used): the stage waits on
-// latency, and at seven it ran 5% slower.  Sharing curves hold theirs in 82 vector
+// Eight waves per SIMD (at most 64 VGPRs): the stage waits on
+// latency, and at seven it ran 5% slower.  Sharing curves hold theirs in 94 vector
 // registers; held to 64 they spill (73 us).
 //
 // kPacked: d_gauss holds nine floats per Gaussian, and the nine planes are
-// written to planes as they are read.
+// written to planes as they are read; rec: the records stage 1 ran on.
 template <int NT, bool kPacked>
 __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_waves_per_eu(NT < kWave ? 5 : 8, 8))) void k_bwd_curves(bz_curves c, int lk, int lg, double inv_rho2,
                                                    double s0, const float *__restrict__ d_gauss,
                                                    float *__restrict__ planes,
+                                                   const float4 *__restrict__ rec,
                                                    int64_t ng, float *__restrict__ d_ctrl,
                                                    float *__restrict__ d_width,
                                                    float *__restrict__ d_color,
@@ -1311,17 +1332,24 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
         const float tr = closed ? v.tau[r] : 0.f, t1 = 1.f - tr;
         float dax = DA[kb].x, day = DA[kb].y;
         float vx = DA[km].x, vy = DA[km].y;
+        float chords = fabsf(vx) + fabsf(vy);
         if (two) {
-            vx += DA[km + 1].x;
-            vy += DA[km + 1].y;
+            const float2 a1 = DA[km + 1];
+            vx += a1.x;
+            vy += a1.y;
+            chords += fabsf(a1.x) + fabsf(a1.y);
         }
         float dyx = 0.f, dyy = 0.f, sy2;
         if (closed) {
             float bx = DB[km].x, by = DB[km].y;
+            float chords_b = fabsf(bx) + fabsf(by);
             if (two) {
-                bx += DB[km + 1].x;
-                by += DB[km + 1].y;
+                const float2 b1 = DB[km + 1];
+                bx += b1.x;
+                by += b1.y;
+                chords_b += fabsf(b1.x) + fabsf(b1.y);
             }
+            chords = fmaf(tr, chords_b, t1 * chords);
             vx = fmaf(tr, bx, t1 * vx);
             vy = fmaf(tr, by, t1 * vy);
             dax = fmaf(tr, DB[kb].x, t1 * dax);
@@ -1335,9 +1363,24 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             sy2 = v.width * v.width + (float)s0;
         }
         const float sx2 = (dax * dax + day * day) * rho2f + (float)s0;
-        const float nv2 = vx * vx + vy * vy;
+        float nv2 = vx * vx + vy * vy;
+        const bool turns = nv2 < 1e-4f * chords * chords;
+        if (!kPacked && turns) {
+            const float2 chord = chord_between(v, (double)tr, km, km + (two ? 2 : 1));
+            vx = chord.x;
+            vy = chord.y;
+            nv2 = vx * vx + vy * vy;
+        }
         const float inv_nv = nv2 > 0.f ? __frsqrt_rn(nv2) : 0.f;
-        const float cs = nv2 > 0.f ? vx * inv_nv : 1.f, sn = nv2 > 0.f ? vy * inv_nv : 0.f;
+        float cs = nv2 > 0.f ? vx * inv_nv : 1.f, sn = nv2 > 0.f ? vy * inv_nv : 0.f;
+        if (kPacked && turns) {
+            const float4 e = rec[3 * (v.g0 + idx) + 1];
+            const float e2 = fmaf(e.x, e.x, e.y * e.y);
+            if (e2 > 0.f && e2 < 3.0e38f) {                // a Gaussian in no list may have any
+                cs = e.x * __frsqrt_rn(e2);
+                sn = e.y * __frsqrt_rn(e2);
+            }
+        }
         const float ia = __builtin_amdgcn_rcpf(sx2), ib = __builtin_amdgcn_rcpf(sy2);
         // the conic's gradient in the principal frame: along, across and mixed
         float abar, bbar, mixed;
@@ -1345,16 +1388,21 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             abar = dg[2];
             mixed = dg[3];
             bbar = dg[4];
-            dg[2] = cs * cs * abar - cs * sn * mixed + sn * sn * bbar;
-            dg[3] = 2.f * cs * sn * (abar - bbar) + (cs * cs - sn * sn) * mixed;
-            dg[4] = sn * sn * abar + cs * sn * mixed + cs * cs * bbar;
+            // abar may be hundreds of times bbar, and the way back takes bbar from
+            // differences of terms of its size: in double, what is lost is the planes'
+            // rounding alone
+            const double c = cs, s = sn, d = (double)abar - bbar;
+            const double c2 = c * c, s2 = s * s, m = c * s * mixed;
+            dg[2] = (float)(c2 * d + (bbar - m));
+            dg[3] = (float)(2.0 * c * s * d + (c2 - s2) * mixed);
+            dg[4] = (float)(s2 * d + (bbar + m));
 #pragma unroll
             for (int q = 0; q < kGradPlanes; ++q) planes[q * ng + v.g0 + idx] = dg[q];
         } else {
-            const float qxx = dg[2], qxy = dg[3], qyy = dg[4];
-            abar = qxx * cs * cs + qxy * cs * sn + qyy * sn * sn;
-            bbar = qxx * sn * sn - qxy * cs * sn + qyy * cs * cs;
-            mixed = 2.f * cs * sn * (qyy - qxx) + (cs * cs - sn * sn) * qxy;
+            const double qxx = dg[2], qxy = dg[3], qyy = dg[4], c = cs, s = sn;
+            abar = (float)(qxx * c * c + qxy * c * s + qyy * s * s);
+            bbar = (float)(qxx * s * s - qxy * c * s + qyy * c * c);
+            mixed = (float)(2.0 * c * s * (qyy - qxx) + (c * c - s * s) * qxy);
         }
         const float f = 2.f * (-abar * ia * ia) * rho2f;
         const float sy2bar = -bbar * ib * ib;
@@ -1731,14 +1779,15 @@ hipError_t launch_bwd_gauss(const float *rec, int64_t n_gauss, const bz_bins &b,
 constexpr int kShareCurves = 4096;
 
 template <bool kPacked>
-void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, float *planes,
-                   const bz_grads &gr, hipStream_t s) {
+void launch_curves(const bz_curves &c, const bz_opts &o, const float *rec_f, const float *d_gauss,
+                   float *planes, const bz_grads &gr, hipStream_t s) {
+    const float4 *rec = reinterpret_cast<const float4 *>(rec_f);
     const double rho = (double)o.rho, inv_rho2 = 1.0 / (rho * rho), s0 = (double)o.sigma0_sq;
     if (c.max_gauss_per_curve > kSmallCurve) {
         const size_t lds = stage2_lds_bytes(c.max_k, c.max_gauss_per_curve);
         hipLaunchKernelGGL((k_bwd_curves<kCurveThreads, kPacked>), dim3(c.n_curves),
                            dim3(kCurveThreads), lds, s, c, c.max_k, c.max_gauss_per_curve, inv_rho2,
-                           s0, d_gauss, planes, c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color,
+                           s0, d_gauss, planes, rec, c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color,
                            gr.d_opacity);
     }
     if (c.max_gauss_per_curve <= 32 && c.n_curves >= kShareCurves) {
@@ -1748,7 +1797,7 @@ void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, f
         const int64_t lds = share * stage2_lds_bytes(lk, c.max_gauss_per_curve);
         hipLaunchKernelGGL((share == 4 ? k_bwd_curves<16, kPacked> : k_bwd_curves<32, kPacked>),
                            dim3((c.n_curves + share - 1) / share), dim3(kWave), lds, s, c, lk,
-                           c.max_gauss_per_curve, inv_rho2, s0, d_gauss, planes, c.n_gauss,
+                           c.max_gauss_per_curve, inv_rho2, s0, d_gauss, planes, rec, c.n_gauss,
                            gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
         return;
     }
@@ -1756,17 +1805,18 @@ void launch_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss, f
     const int lk = c.max_k < kSmallCurve ? c.max_k : kSmallCurve;
     const int lg = c.max_gauss_per_curve < kSmallCurve ? c.max_gauss_per_curve : kSmallCurve;
     hipLaunchKernelGGL((k_bwd_curves<kWave, kPacked>), dim3(c.n_curves), dim3(kWave),
-                       stage2_lds_bytes(lk, lg), s, c, lk, lg, inv_rho2, s0, d_gauss, planes,
+                       stage2_lds_bytes(lk, lg), s, c, lk, lg, inv_rho2, s0, d_gauss, planes, rec,
                        c.n_gauss, gr.d_ctrl, gr.d_width, gr.d_color, gr.d_opacity);
 }
 
-hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *d_gauss,
-                             float *planes, const bz_grads &gr, hipStream_t s) {
+hipError_t launch_bwd_curves(const bz_curves &c, const bz_opts &o, const float *rec,
+                             const float *d_gauss, float *planes, const bz_grads &gr,
+                             hipStream_t s) {
     if (c.n_curves == 0) return hipSuccess;
     if (planes)
-        launch_curves<true>(c, o, d_gauss, planes, gr, s);
+        launch_curves<true>(c, o, rec, d_gauss, planes, gr, s);
     else
-        launch_curves<false>(c, o, d_gauss, nullptr, gr, s);
+        launch_curves<false>(c, o, nullptr, d_gauss, nullptr, gr, s);
     return hipGetLastError();
 }
 
