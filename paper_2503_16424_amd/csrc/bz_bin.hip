@@ -88,12 +88,6 @@ __device__ inline uint32_t wave_excl_scan(uint32_t v, uint32_t &tot) {
     return x - v;
 }
 
-__device__ inline void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // canvas (W x H) of Gaussian g: the single canvas, or its batch canvas
 __device__ inline void gauss_canvas(const bz_canvas *cv, int n_canvas, int64_t g, int &W, int &H,
                                     int &tiles_x, uint32_t &tile_base) {
@@ -122,7 +116,7 @@ __global__ __launch_bounds__(256) void k_count(const float4 *__restrict__ rec, i
     uint32_t *hb = s_hb[wv];
     if (bucket) {
         for (int i = lane; i < nbk; i += 64) hb[i] = 0u;
-        wave_lds_fence();
+        wave_lds_sync();
     }
     if (g < n) {
         int txc = tiles_x;
@@ -146,7 +140,7 @@ __global__ __launch_bounds__(256) void k_count(const float4 *__restrict__ rec, i
         rects[g] = rc;
     }
     if (bucket) {
-        wave_lds_fence();
+        wave_lds_sync();
         const int64_t eb = g / kEmitBlock;
         if (eb < n_eblk)
             for (int i = lane; i < nbk; i += 64) bucket[(int64_t)i * n_eblk + eb] = hb[i];
@@ -417,7 +411,7 @@ __global__ __launch_bounds__(64) void k_emit(const float4 *__restrict__ rec,
         s_rows[kEmitG] = nrows;
         s_off[nb] = g0 + nb < n ? offs[g0 + nb] : (uint32_t)status[0];
     }
-    wave_lds_fence();
+    wave_lds_sync();
     uint32_t out = s_off[0];                   // next output position
     for (uint32_t c0 = 0; c0 < nrows; c0 += kRowChunk) {
         const uint32_t ci = nrows - c0 < (uint32_t)kRowChunk ? nrows - c0 : (uint32_t)kRowChunk;
@@ -456,7 +450,7 @@ __global__ __launch_bounds__(64) void k_emit(const float4 *__restrict__ rec,
         // the slots past the chunk's last row hold cnt (> every pair index),
         // so the pair search below needs no bound
         for (uint32_t it = ci + t; it <= (uint32_t)kRowChunk; it += 64) s_item_off[it] = cnt;
-        wave_lds_fence();
+        wave_lds_sync();
 #pragma unroll
         for (int j = 0; j < kRowChunk / 64; ++j) {
             const uint32_t it = (uint32_t)t * (kRowChunk / 64) + j;
@@ -483,7 +477,7 @@ __global__ __launch_bounds__(64) void k_emit(const float4 *__restrict__ rec,
             }
         }
         out += cnt;
-        wave_lds_fence();
+        wave_lds_sync();
     }
     // positions of the wave's range no row filled
     for (uint32_t o = out + t; o < s_off[nb]; o += 64) {
@@ -905,18 +899,18 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
         // (carry + marks at or before it)-th of them, carry the number that
         // start before the chunk.
         if (t < kBkChunk / 32) s_gstart[wv][t] = 0u;
-        wave_lds_fence();
+        wave_lds_sync();
         if (has_rows && row0 >= c0 && row0 - c0 < (uint32_t)kBkChunk)
             atomicOr(&s_gstart[wv][(row0 - c0) >> 5], 1u << ((row0 - c0) & 31));
         const uint32_t carry = (uint32_t)__popcll(__ballot(has_rows && row0 < c0));
-        wave_lds_fence();
+        wave_lds_sync();
         {
             const uint32_t pc = t < kBkChunk / 32 ? (uint32_t)__popc(s_gstart[wv][t]) : 0u;
             uint32_t tot_pc;
             const uint32_t pref = wave_excl_scan(pc, tot_pc);
             if (t < kBkChunk / 32) s_gpref[wv][t] = pref;
         }
-        wave_lds_fence();
+        wave_lds_sync();
         // this lane's kBkChunk / 64 items share one word of the marks
         const uint32_t it0 = (uint32_t)t * (kBkChunk / 64);
         const uint32_t mword = s_gstart[wv][it0 >> 5];
@@ -960,7 +954,7 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
         const uint32_t nwords = 2 * ((cnt + 63) / 64);
         if (use_bits)
             for (uint32_t q = t; q < nwords; q += 64) s_start[wv][q] = 0u;
-        wave_lds_fence();
+        wave_lds_sync();
 #pragma unroll
         for (int j = 0; j < kBkChunk / 64; ++j) {
             if (wid[j] != 0u) {
@@ -974,7 +968,7 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
         // so the pair search below needs no bound
         for (uint32_t it = nnz + t; it <= (uint32_t)kBkChunk; it += 64) s_item[wv][it].x = cnt;
         if (c0 == 0) fetch_parts();
-        wave_lds_fence();
+        wave_lds_sync();
         // rounds of 64 consecutive pairs of the chunk, one per lane
         uint32_t seen = 0;                 // row marks before the round
         for (uint32_t r0 = 0; r0 < cnt; r0 += 64) {
@@ -1010,7 +1004,7 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_emit_bucketed(
             if (valid && pos < pe.y)
                 packed[pos] = ((key & 255u) << 24) | (uint32_t)(g0 + gl);
         }
-        wave_lds_fence();
+        wave_lds_sync();
     }
     // every bucket of the block filled exactly
     for (uint32_t i = t; i <= span; i += 64)

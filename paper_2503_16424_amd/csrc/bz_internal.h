@@ -182,6 +182,13 @@ inline int64_t num_pixels(const bz_opts &o) {
     return o.batch ? o.batch->n_pixels : (int64_t)o.width * o.height;
 }
 
+// What the wave's lanes wrote to LDS is read by its other lanes after this.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Canvas of an index inside a batch: the last c whose offset (read by off)
 // is <= i, over the n_canvas + 1 records (empty canvases are skipped).
 template <typename Off>

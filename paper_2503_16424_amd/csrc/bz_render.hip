@@ -52,12 +52,6 @@ __device__ inline int xcd_tile(int b, int run) {
 // short enough for eight of them on every XCD.
 constexpr int kXcdRun = 32;
 
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Minimum over the box [x0,x1]x[y0,y1] (offsets from the mean) of
 // f(d) = qa dx^2 + 2 qb dx dy + qc dy^2, compared against thr.
 __device__ inline bool box_hit(float x0, float x1, float y0, float y1, float qa, float qb,

@@ -20,13 +20,6 @@
 
 namespace bz {
 
-// Wave-level barrier with LDS ordering (the wave's own slice only).
-__device__ inline void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The record's mean and shape of a Gaussian of opacity o.
 __device__ inline void record_shape(const Geom &g, float o, float4 &m, float4 &q) {
     // 1 / sx and sx / sy (scales are positive: sigma0^2 > 0, or the
@@ -86,7 +79,7 @@ __global__ __launch_bounds__(kCurveThreads) __attribute__((amdgpu_waves_per_eu(8
         const int64_t eb0 = (v.g0 + base) / kEmitBlock;
         if (bucketed) {
             for (int i = l; i < 2 * nbk; i += 64) hbw[i] = 0u;
-            wave_sync_lds();
+            wave_lds_sync();
         }
         if (idx < n) {
             int r = idx / v.K, k = idx - r * v.K;
@@ -116,7 +109,7 @@ __global__ __launch_bounds__(kCurveThreads) __attribute__((amdgpu_waves_per_eu(8
             }
         }
         if (bucketed) {
-            wave_sync_lds();
+            wave_lds_sync();
             for (int i = l; i < 2 * nbk; i += 64) {
                 const uint32_t c = hbw[i];
                 if (c) {
@@ -126,13 +119,13 @@ __global__ __launch_bounds__(kCurveThreads) __attribute__((amdgpu_waves_per_eu(8
                 }
             }
         }
-        wave_sync_lds();
+        wave_lds_sync();
         const int valid = 3 * (n - base < 64 ? n - base : 64);   // float4s of this round
         float4 *out = rec + 3 * (v.g0 + base);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
             if (j * 64 + l < valid) out[j * 64 + l] = my[j * 64 + l];
-        wave_sync_lds();
+        wave_lds_sync();
     }
     if (kBin && __builtin_amdgcn_ballot_w64(nonfinite) && l == 0)
         atomicOr((unsigned long long *)&bc.status[1], (unsigned long long)Status::kNonFinite);
@@ -181,13 +174,13 @@ __global__ __launch_bounds__(kCurveThreads) void k_sample_flat(bz_curves c, doub
     }
     // starts of the curves after it, as places in the wave
     s_cnt[w][l] = 0;
-    wave_sync_lds();
+    wave_lds_sync();
     {
         const int p = lo + 1 + l;
         const int64_t at = p < c.n_curves ? c.gauss_off[p] - base : 64;
         if (at < 64) s_cnt[w][at] = 1;
     }
-    wave_sync_lds();
+    wave_lds_sync();
     const uint64_t starts = __ballot(s_cnt[w][l] != 0);
     const int p = lo + __popcll(starts & (~0ull >> (63 - l)));
     float4 *my = s_rec[w];
@@ -230,7 +223,7 @@ __global__ __launch_bounds__(kCurveThreads) void k_sample_flat(bz_curves c, doub
             nonfinite = !finite;
         }
     }
-    wave_sync_lds();
+    wave_lds_sync();
     if (bucketed)
         for (int i = l; i < bc.n_buckets; i += 64)
             bc.bucket[(int64_t)i * bc.n_eblk + base / kEmitBlock] = hb[i];

@@ -111,19 +111,13 @@ __global__ void k_order_counts(bz_curves c, const uint32_t *vals, int32_t *order
 constexpr int kOrderMost = 4096;
 constexpr int kRankMost = 512;
 
-__device__ inline void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Ends with the block's barrier.
 __device__ inline void bitonic_sort(uint64_t *key, int m, int t, int nt) {
     bool wide = false;                          // the step before crossed waves
     for (int k = 2; k <= m; k <<= 1) {
         for (int d = k >> 1; d > 0; d >>= 1) {
             if (wide || d > 64) __syncthreads();
-            else wave_lds_order();
+            else wave_lds_sync();
             wide = d > 64;
             for (int p = t; p < m / 2; p += nt) {
                 const int i = 2 * p - (p & (d - 1));

@@ -425,13 +425,6 @@ __global__ __launch_bounds__(256) void k_igemm(GemmArgs args) {
 // (forward) and 2 (the FP32 side); half as many cost the second layer's input
 // gradient 14%, twice as many the last layers' 15%.
 
-// Wave-level LDS ordering.
-__device__ inline void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // LDS of a block: the filters of its columns, lane by lane; the slice table; the
 // classes; an output tile of 16 pixels per wave.
 __host__ __device__ inline int conv_pitch(int nb, int out_bytes) { return 16 * nb * out_bytes + 16; }
@@ -593,7 +586,7 @@ __global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_step
             }
         }
         if (!via_lds) return;
-        wave_fence();
+        wave_lds_sync();
         int px = px0, piece = ch0;
 #pragma unroll
         for (int it = 0; it < kPieces; ++it) {
@@ -621,7 +614,7 @@ __global__ __launch_bounds__(1024) void k_conv_rows(GemmArgs args, int most_step
                 *reinterpret_cast<uint4 *>(g.out_f + o) = d;
             }
         }
-        wave_fence();
+        wave_lds_sync();
     };
     // Two sets of registers in turn: one chunk's pixels travel while the other's
     // are multiplied, across the ends of classes and tiles too.
