@@ -433,6 +433,8 @@ class Rasterizer:
         if f & STATUS_LIST_MISMATCH:
             raise RuntimeError("libbz tile lists inconsistent (emitted tiles differ from counts)")
         if f & STATUS_OVERFLOW:
+            # reading the pair count waits for the stream, so no kernel queued on it
+            # still uses the buffers that go
             self._alloc_pairs(int(math.ceil(self.pairs_required() * slack)) + 1024)
             return True
         return False
