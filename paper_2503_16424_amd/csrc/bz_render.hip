@@ -1313,9 +1313,12 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
     const int r0 = lane / K, k0 = lane - r0 * K;
     for (int idx = lane, r = r0, k = k0; idx < n; idx += NT) {
         float dg[kGradPlanes];
+        const auto load = [&] {
 #pragma unroll
-        for (int q = 0; q < kGradPlanes; ++q)
-            dg[q] = d_gauss[kPacked ? kGradPlanes * (v.g0 + idx) + q : q * ng + v.g0 + idx];
+            for (int q = 0; q < kGradPlanes; ++q)
+                dg[q] = d_gauss[kPacked ? kGradPlanes * (v.g0 + idx) + q : q * ng + v.g0 + idx];
+        };
+        if (kPacked) load();
         // stencil (Eq. sigma with nearest-neighbour ends, Eq. rotation).  Row
         // r's samples are (1 - tau_r) XA + tau_r XB, so its differences along
         // the row are the same blend of DA and DB, and across rows
@@ -1333,7 +1336,6 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             vy += a1.y;
             chords += fabsf(a1.x) + fabsf(a1.y);
         }
-        float dyx = 0.f, dyy = 0.f, sy2;
         if (closed) {
             float bx = DB[km].x, by = DB[km].y;
             float chords_b = fabsf(bx) + fabsf(by);
@@ -1348,6 +1350,20 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             vy = fmaf(tr, by, t1 * vy);
             dax = fmaf(tr, DB[kb].x, t1 * dax);
             day = fmaf(tr, DB[kb].y, t1 * day);
+        }
+        float nv2 = vx * vx + vy * vy;
+        const bool turns = nv2 < 1e-4f * chords * chords;
+        if (!kPacked) {
+            if (turns) {
+                const float2 chord = chord_between(v, (double)tr, km, km + (two ? 2 : 1));
+                vx = chord.x;
+                vy = chord.y;
+                nv2 = vx * vx + vy * vy;
+            }
+            load();                              // not held over the branch above
+        }
+        float dyx = 0.f, dyy = 0.f, sy2;
+        if (closed) {
             const int ra = r < R1 ? r + 1 : R1, rb = r < R1 ? r : R1 - 1;
             const float dt = v.tau[ra] - v.tau[rb];
             dyx = dt * Wd[k].x;
@@ -1357,14 +1373,6 @@ __global__ __launch_bounds__(NT < kWave ? kWave : NT) __attribute__((amdgpu_wave
             sy2 = v.width * v.width + (float)s0;
         }
         const float sx2 = (dax * dax + day * day) * rho2f + (float)s0;
-        float nv2 = vx * vx + vy * vy;
-        const bool turns = nv2 < 1e-4f * chords * chords;
-        if (!kPacked && turns) {
-            const float2 chord = chord_between(v, (double)tr, km, km + (two ? 2 : 1));
-            vx = chord.x;
-            vy = chord.y;
-            nv2 = vx * vx + vy * vy;
-        }
         const float inv_nv = nv2 > 0.f ? __frsqrt_rn(nv2) : 0.f;
         float cs = nv2 > 0.f ? vx * inv_nv : 1.f, sn = nv2 > 0.f ? vy * inv_nv : 0.f;
         if (kPacked && turns) {
