@@ -1144,10 +1144,10 @@ __device__ inline void bwd_tile(const TileArgs &a, int tile) {
     }
 }
 
-// Bound by VALU issue: 565 M instructions on the 2048x2048 frame (11.1 M slots),
-// about 80% of the SIMD cycles.  1,480 us in the form of one lane per pixel with a
-// 64-lane reduction per slot, float LDS atomics and plane atomics; 1,075 us in
-// this one (2040x1344 with 2,048 closed curves: 867 -> 630; 128x128: 101 -> 55, where
+// Bound by VALU issue: 583 M instructions on the 2048x2048 frame (11.1 M slots), on
+// all of the SIMD cycles.  1,480 us in the form of one lane per pixel with a
+// 64-lane reduction per slot, float LDS atomics and plane atomics; 1,010-1,050 us in
+// this one (2040x1344 with 2,048 closed curves: 867 -> 600-645; 128x128: 101 -> 57, where
 // one staging per 64 entries instead of per batch shortens the chain of loads).
 // Products on the matrix cores (v_mfma_f32_16x16x4_f32 for u, w, c . g and the
 // sums) measured no faster than the first form: FP32 products issue at the
